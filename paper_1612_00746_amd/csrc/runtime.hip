@@ -30,6 +30,7 @@
 #include "ctqw_internal.hpp"
 #include "adjoint_pipe.hpp"
 #include "step3c.hpp"
+#include "resident.hpp"
 #include "noise.hpp"
 #include "density.hpp"
 #include "graph.hpp"
@@ -1086,9 +1087,65 @@ ctqw_status enqueue_telegraph(ctqw_plan* p) {
     return CTQW_OK;
 }
 
+// Whether the plan's steps run on chip (resident.hpp), and in which shape.
+bool resident_ok(const ctqw_plan* p, ResidentShape* s) {
+    const ctqw_problem& pr = p->prob;
+    // passes asked for, or a Hamiltonian that changes between steps
+    if (pr.m != 2 || p->launch.chunked || p->tele_amp > 0.0) return false;
+    const int layout = pr.statistics != CTQW_DISTINGUISHABLE ? kResTri
+                                                              : (pr.boundary == CTQW_PERIODIC ? kResRing : kResFull);
+    return resident_shape(layout, pr.dtype == CTQW_C128 ? 1 : 0, pr.accumulation == CTQW_ACC_KAHAN ? 1 : 0, p->max_N,
+                          p->levels, pr.R, s);
+}
+
+// `steps` steps from `in` in one launch, norm checks included.  stride > 0:
+// every step's state is stored, step s at out + s * stride.
+ctqw_status enqueue_resident(ctqw_plan* p, const ResidentShape& s, const void* in, void* out, int64_t stride,
+                             int64_t steps, bool monitor) {
+    const Layout& L = p->lay;
+    const ctqw_problem& pr = p->prob;
+    ResidentArgs a{};
+    a.psi_in = in;
+    a.psi_out = out;
+    a.out_stride = stride;
+    a.reals = at<RealDev>(p, L.reals);
+    a.Jt = s.dtype ? static_cast<const void*>(at<double>(p, L.Jd)) : static_cast<const void*>(at<float>(p, L.Jf));
+    a.Et = s.dtype ? static_cast<const void*>(at<double>(p, L.Ed)) : static_cast<const void*>(at<float>(p, L.Ef));
+    a.scale = at<double>(p, L.scale);
+    a.norm2 = monitor ? at<double>(p, L.norm2) : nullptr;
+    a.tail2 = at<double>(p, L.tail2);
+    a.status = at<int32_t>(p, L.status);
+    a.steps = steps;
+    a.dt = pr.dt;
+    a.tol2 = pr.taylor_tol > 0 ? pr.taylor_tol * pr.taylor_tol : 0.0;
+    a.norm_alarm = pr.norm_alarm;
+    a.renormalize = pr.renormalize;
+    a.one_order = (p->chunk || p->one_depth) ? p->levels : 0;
+    double prod = 1.0;
+    for (int j = 0; j <= kResidentMaxOrder; ++j) {
+        prod *= j > 1 ? j : 1;
+        a.coef[j] = 1.0 / prod;
+    }
+    HIP_TRY(p, launch_resident(s, a, pr.R, p->stream));
+    return CTQW_OK;
+}
+
+// `steps` steps of the current state on chip, timed as one launch.
+ctqw_status enqueue_resident_steps(ctqw_plan* p, const ResidentShape& s, int64_t steps) {
+    ctqw_status st;
+    if (p->timing && (st = record_event(p, 0)) != CTQW_OK) return st;
+    if ((st = enqueue_resident(p, s, p->psi[p->cur], p->psi[p->cur], 0, steps, true)) != CTQW_OK) return st;
+    if (p->timing && (st = record_event(p, 1, steps)) != CTQW_OK) return st;
+    p->steps_done += steps;
+    p->have_step_stats = true;
+    return CTQW_OK;
+}
+
 ctqw_status enqueue_step(ctqw_plan* p) {
     if (p->prob.m == 3) return enqueue_step3(p);
     ctqw_status st;
+    ResidentShape rs;
+    if (resident_ok(p, &rs)) return enqueue_resident_steps(p, rs, 1);
     if ((st = enqueue_telegraph(p)) != CTQW_OK) return st;
     if (p->timing && (st = record_event(p, 0)) != CTQW_OK) return st;
     if ((st = enqueue_step_kernels(p, p->psi[p->cur], p->psi[1 - p->cur])) != CTQW_OK) return st;
@@ -1118,6 +1175,8 @@ ctqw_status collect_timing(ctqw_plan* p);
 // capture stream and the executable graph is replayed on the bound stream.
 ctqw_status enqueue_steps(ctqw_plan* p, int64_t count) {
     if (count <= 0) return CTQW_OK;
+    ResidentShape rs;
+    if (resident_ok(p, &rs)) return enqueue_resident_steps(p, rs, count);
     if (!p->launch.use_graph || count < 2) {
         for (int64_t s = 0; s < count; ++s) {
             ctqw_status st = enqueue_step(p);
@@ -2458,16 +2517,18 @@ ctqw_status ctqw_forward_ckpt(ctqw_plan* p, int64_t n_steps, int64_t ckpt_every,
     const int64_t C = ckpt_every;
     // forward, keeping the state at steps 0, C, 2C, ...; every realisation
     // runs the batch's largest order, the polynomial the adjoint inverts
-    p->one_depth = true;
-    for (int64_t k = 0; k < n_steps; ++k) {
+    ResidentShape rs;
+    const bool resident = resident_ok(p, &rs);
+    for (int64_t k = 0; k < n_steps;) {
         if (k % C == 0)
             HIP_TRY(p, hipMemcpyAsync(G + g.ckpt + (k / C) * g.S, p->psi[p->cur], bytes, hipMemcpyDeviceToDevice, s));
-        if ((st = enqueue_step(p)) != CTQW_OK) {
-            p->one_depth = false;
-            return st;
-        }
+        const int64_t run = resident ? std::min(C, n_steps - k) : 1;
+        p->one_depth = true;
+        st = resident ? enqueue_resident_steps(p, rs, run) : enqueue_step(p);
+        p->one_depth = false;
+        if (st != CTQW_OK) return st;
+        k += run;
     }
-    p->one_depth = false;
     if (n_steps == 0) HIP_TRY(p, hipMemcpyAsync(G + g.ckpt, p->psi[p->cur], bytes, hipMemcpyDeviceToDevice, s));
     p->grad_ws = gws;
     p->grad_steps = n_steps;
@@ -2550,16 +2611,23 @@ ctqw_status ctqw_backward(ctqw_plan* p, int32_t kind, const double* site_w, void
         return (left + passes - 1) / passes;
     };
 
+    ResidentShape rs;
+    const bool resident = resident_ok(p, &rs);
     int lc = 0;   // state(g.lam, lc) holds lambda_{k+1}
     std::vector<const void*> segp(C), vp(n);
     for (int64_t sg = g.n_ckpt - 1; sg >= 0 && n_steps > 0; --sg) {
         const int64_t k0 = sg * C;
         const int64_t len = std::min(C, n_steps - k0);
         segp[0] = state(g.ckpt, sg);
-        for (int64_t k = 1; k < len; ++k) {
-            segp[k] = state(g.seg, k - 1);
-            if ((st = enqueue_step_io(p, segp[k - 1], const_cast<void*>(segp[k]))) != CTQW_OK) return st;
+        for (int64_t k = 1; k < len; ++k) segp[k] = state(g.seg, k - 1);
+        if (resident && len > 1) {
+            p->one_depth = true;
+            st = enqueue_resident(p, rs, segp[0], state(g.seg, 0), g.S, len - 1, false);
+            p->one_depth = false;
+            if (st != CTQW_OK) return st;
         }
+        for (int64_t k = 1; k < len && !resident; ++k)
+            if ((st = enqueue_step_io(p, segp[k - 1], const_cast<void*>(segp[k]))) != CTQW_OK) return st;
         for (int64_t k = len - 1; k >= 0; --k) {
             const void* lam = state(g.lam, lc);
             // v_i = A^i psi_k, K levels per pass, every level stored
