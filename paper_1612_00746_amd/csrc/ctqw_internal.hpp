@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <stdint.h>
 
 namespace ctqw {
@@ -141,26 +142,39 @@ struct InitArgs {
 };
 hipError_t launch_init(const InitArgs& a, hipStream_t stream);
 
+// A group (realisations of one lattice size) as the observable kernels see it.
+struct ObsGroup {
+    int32_t N;
+    int32_t first, last;     // its entries of group_members
+    int32_t panels, chunks;  // column panels and row chunks of the tiles
+    int32_t segs;            // segments of the realisations
+    int32_t block0;          // first block of the tile kernel
+    int32_t pad;
+    int64_t row_off;         // row_part: [segs][panels][N]
+    int64_t col_off;         // col_part: [segs][chunks][N]
+    int64_t pair_off;        // pair_part: [segs][N][N]
+    int64_t out_off;         // the group's block in a snapshot
+};
 struct ObsArgs {
     const void* psi;
     const RealDev* reals;
     const double* scale;
-    double* colsum;              // [sum_r N_r]
-    double* rowsum;              // [sum_r N_r]
-    double* diag;                // [sum_r N_r] p(i, i) (two particles)
-    const int64_t* site_off;     // [R] offsets into the per-site arrays
     const int32_t* group_members;  // realisations ordered by group
-    const int32_t* group_first;  // [G + 1]
-    const int32_t* group_N;      // [G]
-    const int64_t* group_out;    // [G] offset of the group's block in out
-    double* out;                 // device snapshot buffer
-    int64_t R;
+    const ObsGroup* groups;  // [G]
+    double* row_part;
+    double* col_part;
+    double* pair_part;
+    double* out;             // device snapshot buffer
     int32_t G;
     int32_t m;
     int32_t max_N;
+    int32_t blocks;          // of the tile kernel
     int32_t want_pair;
+    int32_t triangle;
     int dtype;
 };
+void obs_tiles(int m, int N, int32_t* panels, int32_t* chunks);
+int obs_rows_per_pass(int m);   // realisations a tile takes at a time
 hipError_t launch_observables(const ObsArgs& a, hipStream_t stream);
 
 struct RescaleArgs {
@@ -173,6 +187,7 @@ struct RescaleArgs {
 hipError_t launch_rescale(const RescaleArgs& a, hipStream_t stream);
 
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t stream);
+hipError_t launch_copy(void* dst, const void* src, int64_t bytes, hipStream_t stream);
 
 // ------------------------------------------------------- three particles
 // Three particles, K terms chained per pass: one work item is a tile of the
@@ -219,22 +234,23 @@ struct Step3cArgs {
 int step3c_rows_per_block(int dtype, int K);
 hipError_t launch_step3c(const Step3cArgs& a, int dtype, int K, hipStream_t stream);
 
+// Three particles have one lattice size, so one group: realisations 0 .. R - 1
+// back to back in the state.
 struct Obs3Args {
     const void* psi;
-    const RealDev* reals;
     const double* scale;
-    double* M;               // [R][3][N][N] two-body marginals
-    double* occ_terms;       // [G][N][N]
-    const int32_t* group_members;
-    const int32_t* group_first;
-    const int32_t* group_N;
-    const int64_t* group_out;
+    double* M;               // partial marginals: 12, 13, 23
+    double* E;               // [3][N][N] their sums over the blocks, per realisation
     double* out;
     int64_t R;
-    int32_t G;
+    int64_t off13, off23;    // of the partials in M; 12 at 0
+    int64_t partials;        // entries of M
     int32_t max_N;
     int32_t want_pair;
+    int32_t panels, chunks;  // tiles along x3 and x2
+    int32_t planes, segs;    // chunks of x1 planes, segments of realisations
 };
+void obs3_split(int N, int64_t R, Obs3Args* a);
 hipError_t launch_obs3(const Obs3Args& a, int dtype, hipStream_t stream);
 
 // ---------------------------------------------------------------- adjoint

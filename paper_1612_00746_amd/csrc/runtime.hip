@@ -55,8 +55,8 @@ struct Region {
 
 struct Layout {
     Region reals, items, order, item_first, claim, lists, Jd, Ed, Jf, Ef, scale, norm_part,
-        tail_part, norm2, tail2, status, colsum, rowsum, diag, site_off, gmembers, gfirst, gN, gout, obs, sites,
-        s3, items3, M3, occ3, chunk, tbase, tsign, tstep;
+        tail_part, norm2, tail2, status, site_off, gmembers, ogroups, orow, ocol, opair, obs, sites,
+        s3, items3, M3, E3, chunk, tbase, tsign, tstep;
     int64_t total = 0;
 };
 
@@ -81,6 +81,10 @@ struct ctqw_plan {
     std::vector<int32_t> group_N, group_first, group_members;
     std::vector<int64_t> group_out;
     int64_t obs_per_snapshot = 0;
+    int64_t obs_slots = 1;           // snapshots held on the device between copies to the host
+    std::vector<ObsGroup> obs_groups;        // m <= 2
+    int64_t obs_rows = 0, obs_cols = 0, obs_pairs = 0;   // partial sums
+    int32_t obs_blocks = 0;
     // work items
     std::vector<ItemDev> items;
     std::vector<Item3Dev> items3;    // three particles: plane tiles
@@ -652,7 +656,6 @@ ctqw_status build_tables(ctqw_plan* p) {
     Layout L;
     const int64_t R = pr.R;
     const int64_t nit = (int64_t)p->items.size();
-    const int64_t G = (int64_t)p->group_N.size();
     align_region(L, L.reals, R * (int64_t)sizeof(RealDev));
     align_region(L, L.items, nit * (int64_t)sizeof(ItemDev));
     align_region(L, L.order, nit * 4);
@@ -669,25 +672,26 @@ ctqw_status build_tables(ctqw_plan* p) {
     align_region(L, L.norm2, R * 8);
     align_region(L, L.tail2, R * 8);
     align_region(L, L.status, 16);
-    align_region(L, L.colsum, p->site_total * 8);
-    align_region(L, L.rowsum, p->site_total * 8);
-    align_region(L, L.diag, p->site_total * 8);
+    align_region(L, L.ogroups, (int64_t)p->obs_groups.size() * (int64_t)sizeof(ObsGroup));
+    align_region(L, L.orow, p->obs_rows * 8);
+    align_region(L, L.ocol, p->obs_cols * 8);
+    align_region(L, L.opair, p->obs_pairs * 8);
     align_region(L, L.site_off, R * 8);
     align_region(L, L.gmembers, R * 4);
-    align_region(L, L.gfirst, (G + 1) * 4);
-    align_region(L, L.gN, G * 4);
-    align_region(L, L.gout, G * 8);
-    align_region(L, L.obs, p->obs_per_snapshot * 8);
+    align_region(L, L.obs, p->obs_slots * p->obs_per_snapshot * 8);
     align_region(L, L.sites, R * pr.m * 4);
     if (pr.m == 3) {
         // tiles, pass buffers (the partial sum and two for the last term of
-        // a pass, used alternately) and the two-body marginals
+        // a pass, used alternately) and the two-body marginals (the blocks'
+        // partials and their sums)
         const int64_t sb = p->state_off.back() * (pr.dtype == CTQW_C128 ? 16 : 8);
         const int64_t NN = (int64_t)p->max_N * p->max_N;
         align_region(L, L.items3, (int64_t)p->items3.size() * (int64_t)sizeof(Item3Dev));
         align_region(L, L.s3, 3 * ((sb + 255) & ~int64_t(255)));
-        align_region(L, L.M3, R * 3 * NN * 8);
-        align_region(L, L.occ3, G * NN * 8);
+        Obs3Args o{};
+        obs3_split(p->max_N, R, &o);
+        align_region(L, L.M3, o.partials * 8);
+        align_region(L, L.E3, 3 * NN * 8);
     }
     if (p->tele_amp > 0.0) {
         // switching noise: baseline hoppings, current signs, step counter
@@ -787,9 +791,8 @@ ctqw_status upload_tables(ctqw_plan* p) {
     HIP_TRY(p, hipMemcpyAsync(p->ws + L.scale.off, ones.data(), L.scale.bytes, h2d, s));
     HIP_TRY(p, hipMemcpyAsync(p->ws + L.site_off.off, p->site_off.data(), L.site_off.bytes, h2d, s));
     HIP_TRY(p, hipMemcpyAsync(p->ws + L.gmembers.off, p->group_members.data(), L.gmembers.bytes, h2d, s));
-    HIP_TRY(p, hipMemcpyAsync(p->ws + L.gfirst.off, p->group_first.data(), L.gfirst.bytes, h2d, s));
-    HIP_TRY(p, hipMemcpyAsync(p->ws + L.gN.off, p->group_N.data(), L.gN.bytes, h2d, s));
-    HIP_TRY(p, hipMemcpyAsync(p->ws + L.gout.off, p->group_out.data(), L.gout.bytes, h2d, s));
+    if (L.ogroups.bytes > 0)
+        HIP_TRY(p, hipMemcpyAsync(p->ws + L.ogroups.off, p->obs_groups.data(), L.ogroups.bytes, h2d, s));
     HIP_TRY(p, launch_fill_zero(p->ws + L.status.off, 32, s));
     if (p->tele_amp > 0.0) {
         HIP_TRY(p, hipMemcpyAsync(p->ws + L.tbase.off, p->Jpad.data(), L.tbase.bytes, h2d, s));
@@ -1232,24 +1235,21 @@ ctqw_status enqueue_steps(ctqw_plan* p, int64_t count) {
     return CTQW_OK;
 }
 
-ctqw_status enqueue_observe(ctqw_plan* p, int want_pair) {
+// The current state's observables into device snapshot `slot`.
+ctqw_status enqueue_observe(ctqw_plan* p, int want_pair, int64_t slot = 0) {
     const Layout& L = p->lay;
+    double* const out = at<double>(p, L.obs) + slot * p->obs_per_snapshot;
     if (p->prob.m == 3) {
         Obs3Args o{};
         o.psi = p->psi[p->cur];
-        o.reals = at<RealDev>(p, L.reals);
         o.scale = at<double>(p, L.scale);
         o.M = at<double>(p, L.M3);
-        o.occ_terms = at<double>(p, L.occ3);
-        o.group_members = at<int32_t>(p, L.gmembers);
-        o.group_first = at<int32_t>(p, L.gfirst);
-        o.group_N = at<int32_t>(p, L.gN);
-        o.group_out = at<int64_t>(p, L.gout);
-        o.out = at<double>(p, L.obs);
+        o.E = at<double>(p, L.E3);
+        o.out = out;
         o.R = p->prob.R;
-        o.G = (int32_t)p->group_N.size();
         o.max_N = p->max_N;
         o.want_pair = want_pair;
+        obs3_split(p->max_N, p->prob.R, &o);
         HIP_TRY(p, launch_obs3(o, p->prob.dtype == CTQW_C128 ? 1 : 0, p->stream));
         return CTQW_OK;
     }
@@ -1257,20 +1257,18 @@ ctqw_status enqueue_observe(ctqw_plan* p, int want_pair) {
     o.psi = p->psi[p->cur];
     o.reals = at<RealDev>(p, L.reals);
     o.scale = at<double>(p, L.scale);
-    o.colsum = at<double>(p, L.colsum);
-    o.rowsum = at<double>(p, L.rowsum);
-    o.diag = at<double>(p, L.diag);
-    o.site_off = at<int64_t>(p, L.site_off);
     o.group_members = at<int32_t>(p, L.gmembers);
-    o.group_first = at<int32_t>(p, L.gfirst);
-    o.group_N = at<int32_t>(p, L.gN);
-    o.group_out = at<int64_t>(p, L.gout);
-    o.out = at<double>(p, L.obs);
-    o.R = p->prob.R;
+    o.groups = at<ObsGroup>(p, L.ogroups);
+    o.row_part = at<double>(p, L.orow);
+    o.col_part = at<double>(p, L.ocol);
+    o.pair_part = at<double>(p, L.opair);
+    o.out = out;
     o.G = (int32_t)p->group_N.size();
     o.m = p->prob.m;
     o.max_N = p->max_N;
+    o.blocks = p->obs_blocks;
     o.want_pair = want_pair;
+    o.triangle = (p->prob.m == 2 && p->prob.statistics != CTQW_DISTINGUISHABLE) ? 1 : 0;
     o.dtype = p->prob.dtype == CTQW_C128 ? 1 : 0;
     HIP_TRY(p, launch_observables(o, p->stream));
     return CTQW_OK;
@@ -1285,26 +1283,28 @@ int64_t snapshot_len(const ctqw_plan* p, uint32_t obs) {
     return n;
 }
 
-// Copy the device snapshot (layout: per group [occ][pair if enabled]) into
-// the caller's layout for the requested observables.
-ctqw_status read_snapshot(ctqw_plan* p, uint32_t obs, double* out) {
-    std::vector<double> host(p->obs_per_snapshot);
-    HIP_TRY(p, hipMemcpyAsync(host.data(), p->ws + p->lay.obs.off, p->lay.obs.bytes, hipMemcpyDeviceToHost,
-                              p->stream));
+// Copy the first `count` device snapshots (layout of each: per group
+// [occ][pair if enabled]) into the caller's layout for the requested
+// observables.
+ctqw_status read_snapshots(ctqw_plan* p, uint32_t obs, int64_t count, double* out) {
+    if (count < 1) return CTQW_OK;
+    std::vector<double> host(count * p->obs_per_snapshot);
+    HIP_TRY(p, hipMemcpyAsync(host.data(), p->ws + p->lay.obs.off, host.size() * 8, hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
     int64_t k = 0;
-    for (size_t g = 0; g < p->group_N.size(); ++g) {
-        const int64_t Ng = p->group_N[g];
-        const double* src = host.data() + p->group_out[g];
-        if (obs & CTQW_OBS_OCCUPATION) {
-            std::memcpy(out + k, src, Ng * 8);
-            k += Ng;
+    for (int64_t n = 0; n < count; ++n)
+        for (size_t g = 0; g < p->group_N.size(); ++g) {
+            const int64_t Ng = p->group_N[g];
+            const double* src = host.data() + n * p->obs_per_snapshot + p->group_out[g];
+            if (obs & CTQW_OBS_OCCUPATION) {
+                std::memcpy(out + k, src, Ng * 8);
+                k += Ng;
+            }
+            if (obs & CTQW_OBS_PAIR) {
+                std::memcpy(out + k, src + Ng, Ng * Ng * 8);
+                k += Ng * Ng;
+            }
         }
-        if (obs & CTQW_OBS_PAIR) {
-            std::memcpy(out + k, src + Ng, Ng * Ng * 8);
-            k += Ng * Ng;
-        }
-    }
     return CTQW_OK;
 }
 
@@ -1320,6 +1320,21 @@ ctqw_status collect_timing(ctqw_plan* p) {
     }
     p->ev_used = 0;
     return CTQW_OK;
+}
+
+// Whether a state copy between the caller's buffer and `mine` may run as a
+// kernel: device memory of the same device, aligned, apart from `mine`.
+// Anything else (another device's memory, an odd address) is the runtime's.
+bool kernel_copies(int32_t on_device, const void* theirs, const void* mine, int64_t bytes) {
+    if (!on_device || (reinterpret_cast<uintptr_t>(theirs) & 15)) return false;
+    const char *a = static_cast<const char*>(theirs), *b = static_cast<const char*>(mine);
+    if (a < b + bytes && b < a + bytes) return false;
+    hipPointerAttribute_t at{}, am{};
+    if (hipPointerGetAttributes(&at, theirs) != hipSuccess || hipPointerGetAttributes(&am, mine) != hipSuccess) {
+        (void)hipGetLastError();   // not known to the runtime: no error of ours
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && am.type == hipMemoryTypeDevice && at.device == am.device;
 }
 
 ctqw_status read_status(ctqw_plan* p, int32_t* st) {
@@ -1463,6 +1478,42 @@ ctqw_status ctqw_plan_create(const ctqw_problem* pr, ctqw_plan** out) {
             if (pr->observables & CTQW_OBS_PAIR) go += (int64_t)kv.first * kv.first;
         }
         p->obs_per_snapshot = go;
+        // up to 64 snapshots, 256 KiB, between copies to the host
+        p->obs_slots = std::max<int64_t>(1, std::min<int64_t>(64, (256 << 10) / (8 * std::max<int64_t>(1, go))));
+        if (pr->m <= 2) {
+            // tiles of every group; few tiles: each group's realisations in as
+            // many segments as bring the launch to four blocks per compute unit
+            constexpr int64_t kObsBlocks = 1024;
+            int64_t tiles = 0;
+            for (size_t g = 0; g < p->group_N.size(); ++g) {
+                ObsGroup o{};
+                o.N = p->group_N[g];
+                o.first = p->group_first[g];
+                o.last = p->group_first[g + 1];
+                o.out_off = p->group_out[g];
+                obs_tiles(pr->m, o.N, &o.panels, &o.chunks);
+                tiles += (int64_t)o.panels * o.chunks;
+                p->obs_groups.push_back(o);
+            }
+            const int64_t want = (kObsBlocks + tiles - 1) / tiles, per = obs_rows_per_pass(pr->m);
+            int64_t blocks = 0;
+            for (ObsGroup& o : p->obs_groups) {
+                o.segs = (int32_t)std::max<int64_t>(1, std::min(want, (o.last - o.first + per - 1) / per));
+                o.block0 = (int32_t)blocks;
+                blocks += (int64_t)o.panels * o.chunks * o.segs;
+                o.row_off = p->obs_rows;
+                o.col_off = p->obs_cols;
+                o.pair_off = p->obs_pairs;
+                if (pr->m == 2) p->obs_rows += (int64_t)o.segs * o.panels * o.N;
+                p->obs_cols += (int64_t)o.segs * o.chunks * o.N;
+                if (pr->m == 2 && (pr->observables & CTQW_OBS_PAIR)) p->obs_pairs += (int64_t)o.segs * o.N * o.N;
+            }
+            if (blocks > INT32_MAX) {
+                delete p;
+                return fail(nullptr, CTQW_ERR_OUT_OF_MEMORY, "too many observable tiles");
+            }
+            p->obs_blocks = (int32_t)blocks;
+        }
         p->launch.cols_per_lane = 1;
         p->launch.waves_per_block = 4;
         p->launch.persistent = 0;
@@ -2114,8 +2165,10 @@ ctqw_status ctqw_set_state(ctqw_plan* p, const void* psi, int32_t on_device) {
     ctqw_status st = ensure_ready(p);
     if (st != CTQW_OK) return st;
     const int64_t bytes = p->state_off.back() * (p->prob.dtype == CTQW_C128 ? 16 : 8);
-    HIP_TRY(p, hipMemcpyAsync(p->psi[0], psi, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                              p->stream));
+    if (kernel_copies(on_device, psi, p->psi[0], bytes)) HIP_TRY(p, launch_copy(p->psi[0], psi, bytes, p->stream));
+    else
+        HIP_TRY(p, hipMemcpyAsync(p->psi[0], psi, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+                                  p->stream));
     std::vector<double> ones(p->prob.R, 1.0);
     HIP_TRY(p, hipMemcpyAsync(p->ws + p->lay.scale.off, ones.data(), p->prob.R * 8, hipMemcpyHostToDevice,
                               p->stream));
@@ -2142,8 +2195,11 @@ ctqw_status ctqw_get_state(ctqw_plan* p, void* psi, int32_t on_device) {
         HIP_TRY(p, launch_rescale(ra, p->stream));
     }
     const int64_t bytes = p->state_off.back() * (p->prob.dtype == CTQW_C128 ? 16 : 8);
-    HIP_TRY(p, hipMemcpyAsync(psi, p->psi[p->cur], bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                              p->stream));
+    if (kernel_copies(on_device, psi, p->psi[p->cur], bytes))
+        HIP_TRY(p, launch_copy(psi, p->psi[p->cur], bytes, p->stream));
+    else
+        HIP_TRY(p, hipMemcpyAsync(psi, p->psi[p->cur], bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                                  p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
     return CTQW_OK;
 }
@@ -2157,7 +2213,7 @@ ctqw_status ctqw_observe(ctqw_plan* p, uint32_t obs, double* out) {
     if (st != CTQW_OK) return st;
     st = enqueue_observe(p, (obs & CTQW_OBS_PAIR) ? 1 : 0);
     if (st != CTQW_OK) return st;
-    return read_snapshot(p, obs, out);
+    return read_snapshots(p, obs, 1, out);
 }
 
 ctqw_status ctqw_propagate(ctqw_plan* p, int64_t n_steps, int64_t output_every, uint32_t obs, double* out) {
@@ -2172,11 +2228,18 @@ ctqw_status ctqw_propagate(ctqw_plan* p, int64_t n_steps, int64_t output_every, 
     if (st != CTQW_OK) return st;
     const int64_t snap = snapshot_len(p, obs);
     const int want_pair = (obs & CTQW_OBS_PAIR) ? 1 : 0;
-    int64_t k = 0;
-    if (outputs) {
-        if ((st = enqueue_observe(p, want_pair)) != CTQW_OK) return st;
-        if ((st = read_snapshot(p, obs, out + (k++) * snap)) != CTQW_OK) return st;
-    }
+    // Snapshots wait on the device, a slot each, and are copied together.
+    int64_t k = 0, held = 0;
+    auto snapshot = [&]() -> ctqw_status {
+        if (held == p->obs_slots) {
+            const ctqw_status e = read_snapshots(p, obs, held, out + k * snap);
+            if (e != CTQW_OK) return e;
+            k += held;
+            held = 0;
+        }
+        return enqueue_observe(p, want_pair, held++);
+    };
+    if (outputs && (st = snapshot()) != CTQW_OK) return st;
     // Steps between outputs form one segment (captured as one graph when
     // use_graph is set); timing collects its events every 256 steps.
     const int64_t seg = outputs ? output_every : (p->timing ? 256 : n_steps);
@@ -2185,11 +2248,9 @@ ctqw_status ctqw_propagate(ctqw_plan* p, int64_t n_steps, int64_t output_every, 
         if ((st = enqueue_steps(p, n)) != CTQW_OK) return st;
         if (p->timing && (st = collect_timing(p)) != CTQW_OK) return st;
         s += n;
-        if (outputs && s % output_every == 0) {
-            if ((st = enqueue_observe(p, want_pair)) != CTQW_OK) return st;
-            if ((st = read_snapshot(p, obs, out + (k++) * snap)) != CTQW_OK) return st;
-        }
+        if (outputs && s % output_every == 0 && (st = snapshot()) != CTQW_OK) return st;
     }
+    if ((st = read_snapshots(p, obs, held, out + k * snap)) != CTQW_OK) return st;
     if ((st = collect_timing(p)) != CTQW_OK) return st;
     int32_t status[4];
     if ((st = read_status(p, status)) != CTQW_OK) return st;
@@ -2521,7 +2582,7 @@ ctqw_status ctqw_forward_ckpt(ctqw_plan* p, int64_t n_steps, int64_t ckpt_every,
     const bool resident = resident_ok(p, &rs);
     for (int64_t k = 0; k < n_steps;) {
         if (k % C == 0)
-            HIP_TRY(p, hipMemcpyAsync(G + g.ckpt + (k / C) * g.S, p->psi[p->cur], bytes, hipMemcpyDeviceToDevice, s));
+            HIP_TRY(p, launch_copy(G + g.ckpt + (k / C) * g.S, p->psi[p->cur], bytes, s));
         const int64_t run = resident ? std::min(C, n_steps - k) : 1;
         p->one_depth = true;
         st = resident ? enqueue_resident_steps(p, rs, run) : enqueue_step(p);
@@ -2529,7 +2590,7 @@ ctqw_status ctqw_forward_ckpt(ctqw_plan* p, int64_t n_steps, int64_t ckpt_every,
         if (st != CTQW_OK) return st;
         k += run;
     }
-    if (n_steps == 0) HIP_TRY(p, hipMemcpyAsync(G + g.ckpt, p->psi[p->cur], bytes, hipMemcpyDeviceToDevice, s));
+    if (n_steps == 0) HIP_TRY(p, launch_copy(G + g.ckpt, p->psi[p->cur], bytes, s));
     p->grad_ws = gws;
     p->grad_steps = n_steps;
     p->grad_ckpt = ckpt_every;
