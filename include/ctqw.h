@@ -176,9 +176,9 @@ typedef struct {
                                 batch with few bands leaves most SIMDs
                                 idle.  0 (default): when the batch has
                                 fewer than 1024 bands, each band's output
-                                rows are split into up to 16 segments
-                                (each at least twice the halo long) to
-                                bring it to about 1024; 1: never split;
+                                rows are split into segments (each at
+                                least twice the halo long) to bring it to
+                                about 1024; 1: never split;
                                 2..16: split into up to that many.  A
                                 segment is swept from halo rows before its
                                 first output row to halo rows after its

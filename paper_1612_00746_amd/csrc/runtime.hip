@@ -42,10 +42,18 @@ namespace {
 
 constexpr int kMaxSites = 32768;
 // Two-particle steps: batches of fewer bands than the device has SIMDs
-// (256 CUs x 4) have their bands' rows split into up to kMaxRowSegments
-// segments.
+// (256 CUs x 4) have their bands' rows split into segments, by default up to
+// kAutoRowSegments, on request up to kMaxRowSegments.  A step lasts as long
+// as one segment's sweep (its rows, twice the halo and the pipeline's depth),
+// so only the smallest useful segment bounds the split: one realisation of
+// N = 1024 (9 bands, order 7) takes 23 us per step in 73 segments of 14
+// rows, 53 in 16 of 64.
 constexpr int kSplitTarget = 1024;
 constexpr int kMaxRowSegments = 16;
+constexpr int kAutoRowSegments = 128;
+// Three particles: a block (8 waves) takes a compute unit, so batches of
+// fewer tiles leave some idle; their x1 planes are split.
+constexpr int64_t kComputeUnits = 256;
 thread_local std::string g_last_error;
 
 struct Region {
@@ -435,36 +443,54 @@ ctqw_status build_tables(ctqw_plan* p) {
         const int rows = step3c_rows_per_block(dtype, k3);
         if (rows <= 0) return fail(p, CTQW_ERR_UNSUPPORTED, "%d terms per pass are not compiled", k3);
         const bool periodic = pr.boundary == CTQW_PERIODIC;
-        for (int64_t r = 0; r < pr.R; ++r) {
-            const int N = p->N[r];
-            std::vector<std::array<int32_t, 3>> yb, zb, trial;
-            if (!bands_1d(N, k3, rows, periodic, 1, yb) || !bands_1d(N, k3, 64, periodic, 1, zb))
-                return fail(p, CTQW_ERR_UNSUPPORTED, "%d terms per pass leave a tile no output", k3);
-            // x3 band boundaries on whole cache lines where that adds no band
-            for (int a = std::max(1, p->launch.band_align / amp_bytes); a > 1; a /= 2) {
-                trial.clear();
-                if (bands_1d(N, k3, 64, periodic, a, trial) && trial.size() <= zb.size()) {
-                    zb.swap(trial);
-                    break;
-                }
+        // every realisation has the same lattice, so the same tiles
+        const int N = p->N[0];
+        std::vector<std::array<int32_t, 3>> yb, zb, trial;
+        if (!bands_1d(N, k3, rows, periodic, 1, yb) || !bands_1d(N, k3, 64, periodic, 1, zb))
+            return fail(p, CTQW_ERR_UNSUPPORTED, "%d terms per pass leave a tile no output", k3);
+        // x3 band boundaries on whole cache lines where that adds no band
+        for (int a = std::max(1, p->launch.band_align / amp_bytes); a > 1; a /= 2) {
+            trial.clear();
+            if (bands_1d(N, k3, 64, periodic, a, trial) && trial.size() <= zb.size()) {
+                zb.swap(trial);
+                break;
             }
+        }
+        // Few tiles: the planes in segments, each swept from k3 planes before its
+        // first output plane to k3 after its last.  A sweep costs its planes and
+        // the pipeline's k3, the launch that times the rounds of blocks; the
+        // cheapest split wins (3 x 61^3 ring, 8 realisations, 64 tiles,
+        // complex128: 45 us per pass in 4 segments, 96 in one).
+        int segs = 1;
+        {
+            const int64_t tiles = (int64_t)yb.size() * (int64_t)zb.size() * pr.R;
+            auto cost = [&](int s) {
+                const int64_t planes = (N + s - 1) / s + (s > 1 || periodic ? 2 * k3 : 0) + k3;
+                return (tiles * s + kComputeUnits - 1) / kComputeUnits * planes;
+            };
+            if (tiles < 2 * kComputeUnits)
+                for (int s = 2; s <= N / (2 * k3); ++s)
+                    if (cost(s) < cost(segs)) segs = s;
+        }
+        for (int64_t r = 0; r < pr.R; ++r) {
             first[r] = (int32_t)items3.size();
             for (const auto& y : yb)
-                for (const auto& zz : zb) {
-                    Item3Dev t{};
-                    t.real = (int32_t)r;
-                    t.z0 = zz[0];
-                    t.zlo = zz[1];
-                    t.zhi = zz[2];
-                    t.y0 = y[0];
-                    t.ylo = y[1];
-                    t.yhi = y[2];
-                    t.x0 = periodic ? -k3 : 0;
-                    t.nplanes = periodic ? N + 2 * k3 : N;
-                    t.plane_lo = 0;
-                    t.plane_hi = N;
-                    items3.push_back(t);
-                }
+                for (const auto& zz : zb)
+                    for (int q = 0; q < segs; ++q) {
+                        Item3Dev t{};
+                        t.real = (int32_t)r;
+                        t.z0 = zz[0];
+                        t.zlo = zz[1];
+                        t.zhi = zz[2];
+                        t.y0 = y[0];
+                        t.ylo = y[1];
+                        t.yhi = y[2];
+                        t.plane_lo = (int32_t)((int64_t)N * q / segs);
+                        t.plane_hi = (int32_t)((int64_t)N * (q + 1) / segs);
+                        t.x0 = periodic ? t.plane_lo - k3 : std::max(0, t.plane_lo - k3);
+                        t.nplanes = (periodic ? t.plane_hi + k3 : std::min(N, t.plane_hi + k3)) - t.x0;
+                        items3.push_back(t);
+                    }
             if (items3.size() > (size_t)INT32_MAX) return fail(p, CTQW_ERR_OUT_OF_MEMORY, "too many tiles");
         }
         first[pr.R] = (int32_t)items3.size();
@@ -503,7 +529,7 @@ ctqw_status build_tables(ctqw_plan* p) {
         // output row to `halo` rows after its last (the rows the pipeline
         // needs to bring its deepest term up to date).
         const int seg_cap = p->launch.row_segments == 0
-                                ? ((int64_t)items.size() < kSplitTarget ? kMaxRowSegments : 1)
+                                ? ((int64_t)items.size() < kSplitTarget ? kAutoRowSegments : 1)
                                 : p->launch.row_segments;
         if (!chunk && pr.m == 2 && seg_cap > 1) {
             const bool periodic = pr.boundary == CTQW_PERIODIC;
