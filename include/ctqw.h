@@ -381,8 +381,7 @@ ctqw_status ctqw_graph_evolve(int32_t n_nodes, int32_t width, const int32_t* nbr
  *                and the on-site energy; read only
  *   psi          device state [R][Ly][Lx], complex, updated in place
  *   workspace    ctqw_lattice_workspace bytes of device memory, 256-byte
- *                aligned (a second state buffer, the dt-scaled tables and
- *                the norm partials)
+ *                aligned (a second state buffer and the norm partials)
  *   norms        device double [n_steps][R] or NULL: the squared FP64
  *                2-norm of each realisation after each step (per band in a
  *                fixed order, then over the bands in band order)
