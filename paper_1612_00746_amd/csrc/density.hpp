@@ -28,7 +28,8 @@ struct HerkArgs {
     void* rho;
     int64_t D, Dp, ld;
     int32_t Rp;
-    int64_t n_tiles;             // T (T + 1) / 2 with T = Dp / tile
+    int64_t tile0;               // first tile of a launch (set by launch_herk)
+    int64_t n_tiles;             // T (T + 1) / 2 with T = Dp / tile; of a launch: its tiles
     double inv_R;
 };
 int herk_tile(int dtype);        // rows of a tile (128 complex64, 64 complex128)
