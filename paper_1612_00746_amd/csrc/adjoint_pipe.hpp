@@ -21,8 +21,8 @@
 // Work item: a band of 64 - 2K output columns of one realisation, held by
 // one wave with K halo columns on either side (level l is exact up to l
 // columns from the window's edges, and the contraction reaches one column
-// further), swept down the rows in kSweepSegs row segments (one wave each)
-// that start K rows before their first output row and end K rows after the
+// further), swept down the rows in row segments (one wave each: kSweepSegs,
+// or kSweepSegsMax where the batch is small) that start K rows before their first output row and end K rows after the
 // last (open chains: clamped to the grid, whose outside is zero).
 #pragma once
 
@@ -31,11 +31,12 @@
 namespace ctqw {
 
 // Levels per pass compiled for each state type: forward-vector passes, and
-// Horner passes (whose contraction holds two more rows per level, and more
-// would spill at two waves per SIMD).
+// Horner passes (whose contraction holds two more rows per level; more would
+// spill at two waves per SIMD: complex128 with three levels spills 40 VGPRs
+// and takes 45 us where two take 19.6, see the kernel's figures).
 constexpr int kPipeMaxLevelsC64 = 8;
 constexpr int kPipeMaxLevelsC128 = 4;
-constexpr int kPipeMaxHornerC64 = 3;
+constexpr int kPipeMaxHornerC64 = 4;
 constexpr int kPipeMaxHornerC128 = 2;
 constexpr int kPipeMaxLevels = 8;
 
@@ -58,7 +59,8 @@ struct AdjPipeArgs {
     double* gR;
     int64_t R;
     int nb;                             // band slots per realisation in gV / gR
-    int max_n;                          // largest chain of the batch (the grid's bands)
+    int max_n;                          // largest chain of the batch
+    int bands;                          // its bands (set by the launcher)
     int row_stride;
     int levels;                         // K
     int dtype;
@@ -74,6 +76,6 @@ inline int pipe_max_levels(int dtype, bool contract) {
     return dtype == 1 ? kPipeMaxLevelsC128 : kPipeMaxLevelsC64;
 }
 
-hipError_t launch_adj_pipe(const AdjPipeArgs& a, hipStream_t stream);
+hipError_t launch_adj_pipe(AdjPipeArgs a, hipStream_t stream);
 
 }  // namespace ctqw

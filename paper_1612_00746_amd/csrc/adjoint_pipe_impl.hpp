@@ -7,17 +7,33 @@
 //     enters, scaled by xs; rows past the sweep enter as zero;
 //   * level l = 1 .. K: row i - l of Y_l from level l - 1's rows
 //     i - l - 1, i - l, i - l + 1 (a 3-row register window per level), plus
-//     cz_l times row i - l of Z; lanes without a stored amplitude (off the
-//     chain, the triangle's lower part) are held at zero; stored if
-//     y[l - 1] is set; and, for the Horner passes, level l's input row
-//     contracted with rows i - l, i - l + 1 of v[l - 1];
+//     cz_l times row i - l of Z; stored if y[l - 1] is set; and, for the
+//     Horner passes, level l's input row contracted with rows i - l,
+//     i - l + 1 of v[l - 1];
 //   * the row parts of row i - K (its last contribution came from level K)
 //     join a batch of three rows, which is summed over the wave at once.
-// Everything that follows a row down the levels -- its Z row, the partner
-// rows of v (fetched three steps ahead), its row parts -- rides in a shift
-// register with one stage per level, so the sweep needs no unrolling beyond
-// the three steps of the row windows (a longer unroll let the compiler keep
-// every step's row addresses in scalar registers at once, which spilled).
+// A row's coefficients (and its Z row, its store offsets, its row parts) are
+// formed once, as the row enters, and wait in rings of U >= K slots while it
+// passes the levels; the sweep is unrolled U rows, so that every slot is a
+// compile-time register.  The coefficients are zero wherever no amplitude is
+// stored (off the chain, the triangle's lower part, rows past the sweep) and
+// hold the triangle's mirrored neighbours on its diagonal, so that a level
+// is ten FMAs with nothing to compare or select, and the contractions need
+// no masks but those of the finished sums: a lane without a stored amplitude
+// multiplies zeros.  The row couplings come through the scalar cache, U rows
+// ahead.
+//
+// Bound, in about equal parts that overlap little, by instruction issue and
+// by the vectors' traffic (two bosons, N = 256, 512 realisations, complex64:
+// six forward levels take 300 us, of which 140 remain without the stores and
+// 140 are the 0.94 GB at a large copy's rate).  Levels that formed their own
+// diagonal, masks and offsets took 32 VALU instructions per row and level
+// forward and 76 in a Horner pass; these take 15 and 47.  Per time step of
+// that gradient (six forward levels, seven Horner levels): 1070 us then in
+// passes of 6, 3, 2, 2 levels, 824 now in passes of 6, 4, 3.  complex128,
+// distinguishable on a ring of 129 sites, 24 realisations (72 bands):
+// passes of two Horner levels 30 -> 19.6 us, of four forward levels 28 ->
+// 18.5 us, where the loads' latency and the row sums' are what is left.
 // Contractions.  Full grid (distinguishable particles; one particle is the
 // one-row case): the column parts of bond c and site c are sums over the
 // rows, kept per lane; the row parts of bond q and site q are sums over the
@@ -47,18 +63,122 @@ using namespace adj;
 
 __host__ __device__ constexpr int mpos(int x, int w) { return ((x % w) + w) % w; }
 
+// The couplings are read-only while a pass runs: through the scalar cache.
+template <typename T>
+using ConstPtr = const __attribute__((address_space(4))) T*;
+
+// Coefficients of one row at this lane's column: the level forms
+// d m + u (row above) + b (row below) + l (left) + r (right).  u and b are
+// per lane for the triangle, whose diagonal mirrors, and uniform otherwise.
+//
+// complex64 is written out so that the neighbouring columns enter through
+// DPP-routed FMAs.  A DPP read of a VGPR must follow the VALU write of that
+// register by two wait states: the DPP instructions come after six VALU
+// instructions of the block, and their sources are inputs of the block.
+//   forward (s = +1): y  = -i h;   Horner (s = -1): y += i h.
+template <typename T, bool LANE_UB, bool NEG>
+__device__ __forceinline__ void stencil(T mr, T mi, T ur, T ui, T dr, T di, T d, T u, T b, T l, T r, T& yr, T& yi,
+                                        T& rr, T& ri) {
+    if constexpr (sizeof(T) == 4) {
+#define CTQW_PIPE_FWD(UB)                                                                    \
+    asm("v_mul_f32 %0, %8, %3\n\t"                                                           \
+        "v_mul_f32 %1, -%8, %2\n\t"                                                          \
+        "v_fma_f32 %0, %9, %5, %0\n\t"                                                       \
+        "v_fma_f32 %1, -%9, %4, %1\n\t"                                                      \
+        "v_fma_f32 %0, %10, %7, %0\n\t"                                                      \
+        "v_fma_f32 %1, -%10, %6, %1\n\t"                                                     \
+        "v_fmac_f32_dpp %0, %3, %11 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"  \
+        "v_fmac_f32_dpp %1, -%2, %11 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t" \
+        "v_fmac_f32_dpp %0, %3, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"  \
+        "v_fmac_f32_dpp %1, -%2, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"     \
+        : "=&v"(yr), "=&v"(yi)                                                               \
+        : "v"(mr), "v"(mi), "v"(ur), "v"(ui), "v"(dr), "v"(di), "v"(d), UB(u), UB(b), "v"(l), "v"(r))
+#define CTQW_PIPE_HORNER(UB)                                                                 \
+    asm("v_fma_f32 %0, -%8, %3, %0\n\t"                                                      \
+        "v_fma_f32 %1, %8, %2, %1\n\t"                                                       \
+        "v_fma_f32 %0, -%9, %5, %0\n\t"                                                      \
+        "v_fma_f32 %1, %9, %4, %1\n\t"                                                       \
+        "v_fma_f32 %0, -%10, %7, %0\n\t"                                                     \
+        "v_fma_f32 %1, %10, %6, %1\n\t"                                                      \
+        "v_fmac_f32_dpp %0, -%3, %11 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t" \
+        "v_fmac_f32_dpp %1, %2, %11 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"  \
+        "v_fmac_f32_dpp %0, -%3, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t" \
+        "v_fmac_f32_dpp %1, %2, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"      \
+        : "+&v"(yr), "+&v"(yi)                                                               \
+        : "v"(mr), "v"(mi), "v"(ur), "v"(ui), "v"(dr), "v"(di), "v"(d), UB(u), UB(b), "v"(l), "v"(r))
+        if constexpr (NEG) {
+            if constexpr (LANE_UB) CTQW_PIPE_HORNER("v");
+            else CTQW_PIPE_HORNER("s");
+        } else {
+            if constexpr (LANE_UB) CTQW_PIPE_FWD("v");
+            else CTQW_PIPE_FWD("s");
+        }
+#undef CTQW_PIPE_FWD
+#undef CTQW_PIPE_HORNER
+    } else {
+        rr = from_right(mr);
+        ri = from_right(mi);
+        const T lr = from_left(mr), li = from_left(mi);
+        const T s = NEG ? T(-1) : T(1);
+        if constexpr (!NEG) yr = yi = T(0);
+        yr = fma(s * d, mi, yr);
+        yi = fma(-s * d, mr, yi);
+        yr = fma(s * u, ui, yr);
+        yi = fma(-s * u, ur, yi);
+        yr = fma(s * b, di, yr);
+        yi = fma(-s * b, dr, yi);
+        yr = fma(s * l, li, yr);
+        yi = fma(-s * l, lr, yi);
+        yr = fma(s * r, ri, yr);
+        yi = fma(-s * r, rr, yi);
+    }
+}
+
+// Im conj(y) v with y = a level's input, in the state's precision: the site
+// (s0), the bond to the right (hb) and, added to vb, the bond below (d: the
+// input's row below, p: v's).  rr, ri: the input's right neighbours (complex128).
+template <typename T>
+__device__ __forceinline__ void contract(T mr, T mi, T dr, T di, T rr, T ri, T vx, T vy, T px, T py, T& s0, T& hb,
+                                         T& vb) {
+    if constexpr (sizeof(T) == 4) {
+        asm("v_mul_f32 %0, %3, %8\n\t"
+            "v_fma_f32 %2, %3, %10, %2\n\t"
+            "v_fma_f32 %0, -%4, %7, %0\n\t"
+            "v_fma_f32 %2, -%4, %9, %2\n\t"
+            "v_fma_f32 %2, %5, %8, %2\n\t"
+            "v_fma_f32 %2, -%6, %7, %2\n\t"
+            "v_mul_f32_dpp %1, %8, %3 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, -%7, %4 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %3, %8 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, -%4, %7 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+            : "=&v"(s0), "=&v"(hb), "+&v"(vb)
+            : "v"(mr), "v"(mi), "v"(dr), "v"(di), "v"(vx), "v"(vy), "v"(px), "v"(py));
+    } else {
+        const T qx = from_right(vx), qy = from_right(vy);
+        s0 = im_t(mr, mi, vx, vy);
+        hb = fma(mr, qy, fma(-mi, qx, fma(rr, vy, -(ri * vx))));
+        vb = fma(mr, py, fma(-mi, px, fma(dr, vy, fma(-di, vx, vb))));
+    }
+}
+
 template <typename T, int K, int LAY, bool PER, bool CON>
-__global__ void __launch_bounds__(64 * kSweepSegs, 2) pipe_kernel(AdjPipeArgs a) {
+__global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs a) {
     using C = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
     constexpr int W = 64 - 2 * K;          // output columns per band
+    constexpr int U = 3 * ((K + 2) / 3);   // ring slots and unrolled rows
     static_assert(K >= 1 && K <= kPipeMaxLevels, "levels per pass");
     static_assert(!(PER && LAY == 2), "no triangle on a ring");
     constexpr bool periodic = PER;          // columns on a ring
     constexpr bool rper = PER && LAY != 0;  // rows on a ring (one particle: a single row)
     constexpr bool tri = LAY == 2;
 
-    const int r = blockIdx.y;
-    const int w = blockIdx.x;
+    // Consecutive blocks go to the XCDs in turn: a realisation's bands are
+    // given to one XCD, whose L2 then holds the halo columns and the lines
+    // that two bands share.
+    const int k8 = blockIdx.x >> 3;
+    const int r = (k8 / a.bands) * 8 + (blockIdx.x & 7);
+    const int w = k8 % a.bands;
+    if (r >= a.R) return;   // whole block, before the barrier
     const RealDev rd = a.reals[r];
     const int N = rd.N, rows = LAY == 0 ? 1 : rd.rows;
     // Bands are laid from the chain's end: band w outputs [hi - W, hi),
@@ -68,14 +188,14 @@ __global__ void __launch_bounds__(64 * kSweepSegs, 2) pipe_kernel(AdjPipeArgs a)
     const int hi_w = N - W * (nbr - 1 - w);
     const int lo_w = max(0, hi_w - W);
     const int lane = threadIdx.x & 63;
+    const int segs = blockDim.x >> 6;   // kSweepSegs or kSweepSegsMax
     const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const T* Jc = reinterpret_cast<const T*>(a.Jt) + rd.param_off;
     const T* Ec = reinterpret_cast<const T*>(a.Et) + rd.param_off;
-    const T* Jr = reinterpret_cast<const T*>(a.Jt) + rd.row_param_off;
-    const T* Er = reinterpret_cast<const T*>(a.Et) + rd.row_param_off;
+    const ConstPtr<T> Jr = (ConstPtr<T>)(reinterpret_cast<uintptr_t>(a.Jt)) + rd.row_param_off;
+    const ConstPtr<T> Er = (ConstPtr<T>)(reinterpret_cast<uintptr_t>(a.Et)) + rd.row_param_off;
     const T Udt = static_cast<T>(rd.U * a.dt);
     const int want = (rd.flags & RF_NEAREST) ? 1 : 0;
-    const T sg = static_cast<T>(a.sign);
     const T xs = static_cast<T>(a.xs);
 
     // this lane's column: window [lo_w - K, lo_w - K + 64), output [lo_w, hi_w)
@@ -87,41 +207,41 @@ __global__ void __launch_bounds__(64 * kSweepSegs, 2) pipe_kernel(AdjPipeArgs a)
     const T jr = (inb && (periodic || c < N - 1)) ? Jc[cw] : T(0);
     const T ec = inb ? Ec[cw] : T(0);
     const bool has_bond_c = periodic || c < N - 1;
-    auto stored = [&](int q) { return inb && (!tri || cw >= q); };
 
     // rows holding a stored amplitude of this window, split into one segment
     // per wave; the sweep runs K rows beyond the segment on either side
     const int q_end = tri ? min(rows, hi_w) : rows;
-    const int q0 = (int)(((int64_t)q_end * seg) / kSweepSegs);
-    const int q1 = (int)(((int64_t)q_end * (seg + 1)) / kSweepSegs);
+    const int seg_bits = segs == kSweepSegs ? 2 : 3;
+    const int q0 = (q_end * seg) >> seg_bits;   // rows < 2^28
+    const int q1 = (q_end * (seg + 1)) >> seg_bits;
     const int s_lo = rper ? q0 - K : max(0, q0 - K);
     const int s_hi = rper ? q1 + K : min(rows, q1 + K);
     const int nsweep = q1 > q0 ? s_hi - s_lo : 0;
     const int o_lo = q0 - s_lo, o_hi = q1 - s_lo;   // output rows, as sweep steps
 
-    const uint32_t col_off = (uint32_t)cw * (uint32_t)sizeof(C);
-    // grid row of sweep step s (wrapped on a ring)
-    auto grid_row = [&](int s) { return rper ? wrapi(s_lo + s, rows) : s_lo + s; };
     // One buffer resource per array over this realisation's amplitudes (the
     // launcher keeps them under 2^31 bytes), the row in the per-lane offset:
     // a 32-bit offset per access instead of a resource per row.  Lanes
-    // without a stored amplitude, and rows outside the sweep, take an offset
-    // past the end: loads read 0 and stores are dropped.
+    // without a stored amplitude (dead), and rows outside a range, take an
+    // offset past the end: loads read 0 and stores are dropped.
+    const uint32_t col_off = (uint32_t)cw * (uint32_t)sizeof(C);
+    const uint32_t dead = inb ? 0u : kPastEnd;
+    const uint32_t dead_out = out ? 0u : kPastEnd;
     const uint32_t real_bytes =
         (uint32_t)(tri ? N * (N + 1) / 2 : rows * N) * (uint32_t)sizeof(C);
     auto arr_rsrc = [&](const void* base) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<C*>(reinterpret_cast<const C*>(base)) + rd.state_off, 0,
                                                  base ? (int)real_bytes : 0, kRawBufferWord3);
     };
-    auto lane_off = [&](int s) -> uint32_t {
-        int q = s_lo + s;
-        const bool live = s >= 0 && s < nsweep;
-        if (rper) q = wrapi(q, rows);
-        q = live ? q : 0;
+    // offset of grid row q at this lane's column, past the end unless in_row
+    auto row_off = [&](int q, bool in_row, uint32_t dead_lanes) -> uint32_t {
         const uint32_t rowb = (uint32_t)(tri ? q * N - (q * (q + 1)) / 2 : q * N) * (uint32_t)sizeof(C);
-        return (live && stored(q)) ? rowb + col_off : kPastEnd;
+        const uint32_t base = in_row ? rowb : kPastEnd;
+        const uint32_t dl = (tri && cw < q) ? kPastEnd : dead_lanes;
+        return (base + col_off) | dl;
     };
-    auto ldrow = [&](const __amdgpu_buffer_rsrc_t rs, int s) -> C { return load_c(rs, lane_off(s), (C*)nullptr); };
+    // the next row of the grid (rows past an open grid are never in range)
+    auto next_row = [&](int q) { return (rper && q + 1 == rows) ? 0 : q + 1; };
 
     // The Horner passes (CON) add Z to every level; the forward passes have none.
     const bool x_is_z = CON && a.x == a.z;
@@ -138,210 +258,206 @@ __global__ void __launch_bounds__(64 * kSweepSegs, 2) pipe_kernel(AdjPipeArgs a)
 
     T yr[K][3], yi[K][3];          // levels 0 .. K - 1, rows modulo 3
     C xq[3], zq[3];                // X and Z rows i .. i + 2, modulo 3
-    // Row couplings, read three steps ahead and handed down the levels:
-    // pjd[l] / pe[l] = the bond below / the on-site energy of row i - l
-    // (0 off the grid; an open chain's last bond is 0 in the tables), so
-    // that row's bond above is pjd[l + 1].
-    T qjd[3], qe[3];               // rows i .. i + 2, modulo 3
-    T pjd[K + 2], pe[K + 1];
-    T zr[CON ? K + 1 : 1], zi[CON ? K + 1 : 1];   // zr[l]: Z row i - l (stage l of the shift register)
-    C vq[CON ? K : 1][3];          // vq[l - 1][k]: v[l - 1] row i - l + k
-    T rpv[CON ? K + 1 : 1], rps[CON ? K + 1 : 1];   // row parts of row i - l after level l
+    // rings over the rows in flight, slot = row modulo U
+    T cd[U];                       // diagonal
+    T cu[tri ? U : 1], cb[tri ? U : 1], cl[tri ? U : 1], cr[tri ? U : 1];
+    T sb[U], sb_last = T(0);       // full grid: the bond below the row; sb_last: row i - K - 1's
+    uint32_t so[U];                // store offset
+    uint32_t vo[CON ? U : 1];      // load offset of v (rows i + 2 .. i + 3 - K)
+    T zr[CON ? U : 1], zi[CON ? U : 1];
+    T rpv[CON ? U : 1], rps[CON ? U : 1];   // row parts so far
+    C vq[CON ? K : 1][3];          // v[l - 1] rows i - l .. i - l + 2, modulo 3
     double batch[8];               // three completed rows (bond, site), two zeros
-    // Lane offsets of the rows a step touches, formed once per row as it
-    // enters: after step i's shift ro[j] is the offset of row i + 3 - j
-    // (X and Z load row i + 3, level l loads v[l - 1] row i - l + 3 and
-    // stores row i - l).
-    uint32_t ro[K + 4];
-#pragma unroll
-    for (int j = 0; j < K + 4; ++j) ro[j] = lane_off(2 - j);
+    T gj[U], ge[U], nj[U], ne[U];  // couplings of this and the next U rows: the bond below, the energy
+
 #pragma unroll
     for (int l = 0; l < K; ++l)
 #pragma unroll
         for (int k = 0; k < 3; ++k) yr[l][k] = yi[l][k] = T(0);
 #pragma unroll
-    for (int l = 0; l <= (CON ? K : 0); ++l) zr[l] = zi[l] = T(0);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) batch[k] = 0.0;
-    // couplings of sweep step s (zero off the grid)
-    auto row_jd = [&](int s) -> T {
-        const int q = s_lo + s;
-        if (LAY == 0 || s < 0 || s >= nsweep || (!rper && (q < 0 || q >= rows - 1))) return T(0);
-        return Jr[rper ? wrapi(q, rows) : q];
-    };
-    auto row_e = [&](int s) -> T {
-        const int q = s_lo + s;
-        if (s < 0 || s >= nsweep || (!rper && (q < 0 || q >= rows))) return T(0);
-        return Er[rper ? wrapi(q, rows) : q];
-    };
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        xq[k] = ldrow(X, k);
-        if constexpr (CON) zq[k] = ldrow(Z, k);
-        qjd[k] = row_jd(k);
-        qe[k] = row_e(k);
+    for (int k = 0; k < U; ++k) {
+        cd[k] = sb[k] = T(0);
+        so[k] = kPastEnd;
+        if constexpr (tri) cu[k] = cb[k] = cl[k] = cr[k] = T(0);
+        if constexpr (CON) {
+            vo[k] = kPastEnd;
+            zr[k] = zi[k] = rpv[k] = rps[k] = T(0);
+        }
     }
 #pragma unroll
-    for (int l = 0; l <= K + 1; ++l) pjd[l] = T(0);
+    for (int k = 0; k < 8; ++k) batch[k] = 0.0;
+
+    const int first = rper ? wrapi(s_lo, rows) : s_lo;
+    int qi = first;                // grid row of sweep step i
+    int qx = first;                // of step i + 3
+    int qn = first;                // of the next group's first row
+    const int last = rows - 1;
+    auto load_group = [&](T (&j)[U], T (&e)[U]) {
 #pragma unroll
-    for (int l = 0; l <= K; ++l) pe[l] = T(0);
-    // before step i's shift pjd[l] holds row i - 1 - l: at the start, the
-    // bond above the sweep's first row (a ring, or a segment inside the grid)
-    pjd[0] = (LAY != 0 && (rper || s_lo > 0)) ? Jr[rper ? wrapi(s_lo - 1, rows) : max(s_lo - 1, 0)] : T(0);
+        for (int k = 0; k < U; ++k) {
+            const int q = min(qn, last);
+            j[k] = LAY == 0 ? T(0) : Jr[q];
+            e[k] = Er[q];
+            qn = next_row(qn);
+        }
+    };
+    load_group(nj, ne);
+    T above = T(0);                // the bond above row i (the row above the sweep holds zeros)
+    // rows 0 .. 2 of X and Z, and of v where a level has them in its window
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t off = row_off(qx, k < nsweep, dead);
+        xq[k] = load_c(X, off, (C*)nullptr);
+        if constexpr (CON) {
+            zq[k] = load_c(Z, off, (C*)nullptr);
+            vo[mpos(k, U)] = row_off(qx, k >= o_lo && k <= o_hi && k < nsweep, dead);
+        }
+        qx = next_row(qx);
+    }
     if constexpr (CON) {
-#pragma unroll
-        for (int l = 0; l <= K; ++l) rpv[l] = rps[l] = T(0);
+        // level l starts with rows -l .. 2 - l of its v
 #pragma unroll
         for (int l = 1; l <= K; ++l)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) vq[l - 1][k] = ldrow(V[l - 1], k - l);
+            for (int k = 0; k < 3; ++k) {
+                if (k - l >= 0) vq[l - 1][mpos(k - l, 3)] = load_c(V[l - 1], vo[mpos(k - l, U)], (C*)nullptr);
+                else vq[l - 1][mpos(k - l, 3)].x = vq[l - 1][mpos(k - l, 3)].y = T(0);
+            }
     }
     double bond_col = 0.0, site_col = 0.0;
     const double f = tri ? 2.0 : 1.0;
-    double* gV = a.gV + ((int64_t)r * a.nb + w) * a.row_stride;
-    double* gR = a.gR + ((int64_t)r * a.nb + w) * a.row_stride;
+    // Row sums: lane 8 j holds value j of a batch (rows i - K - 2 .. i - K,
+    // bond and site).  Each is read one batch ahead of its addition; a row is
+    // in one segment of one band, so no other wave touches it.
+    double* g_row = ((lane & 8) ? a.gR : a.gV) + ((int64_t)r * a.nb + w) * a.row_stride;
+    const int j_row = lane >> 4;
+    auto holds_row = [&](int s) { return (lane & 7) == 0 && j_row < 3 && s >= o_lo && s < o_hi; };
+    double g_old = 0.0;
+    if (CON && LAY != 0) {
+        const int s = -K + j_row;
+        if (holds_row(s)) g_old = g_row[s_lo + s];
+    }
 
     const int total = nsweep > 0 ? nsweep + K : 0;
-    for (int i0 = 0; i0 < total; i0 += 3) {
+    for (int i0 = 0; i0 < total; i0 += U) {
 #pragma unroll
-        for (int u = 0; u < 3; ++u) {
+        for (int k = 0; k < U; ++k) {
+            gj[k] = nj[k];
+            ge[k] = ne[k];
+        }
+        load_group(nj, ne);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             const int i = i0 + u;
-            // ---- level 0: row i enters (zero past the sweep)
-            {
-                const bool in = i < nsweep;
-                const C xv = (CON && x_is_z) ? zq[u] : xq[u];
-                yr[0][u] = in ? xs * xv.x : T(0);
-                yi[0][u] = in ? xs * xv.y : T(0);
-                if constexpr (CON) {
-                    // the Z shift register advances one stage
-#pragma unroll
-                    for (int l = K; l >= 1; --l) {
-                        zr[l] = zr[l - 1];
-                        zi[l] = zi[l - 1];
-                    }
-                    zr[0] = zq[u].x;
-                    zi[0] = zq[u].y;
-                }
-#pragma unroll
-                for (int l = K + 1; l >= 1; --l) pjd[l] = pjd[l - 1];
-#pragma unroll
-                for (int l = K; l >= 1; --l) pe[l] = pe[l - 1];
-                pjd[0] = qjd[u];
-                pe[0] = qe[u];
-#pragma unroll
-                for (int j = K + 3; j >= 1; --j) ro[j] = ro[j - 1];
-                ro[0] = lane_off(i + 3);
-                xq[u] = load_c(X, ro[0], (C*)nullptr);
-                if constexpr (CON) zq[u] = load_c(Z, ro[0], (C*)nullptr);
-                qjd[u] = row_jd(i + 3);
-                qe[u] = row_e(i + 3);
-            }
+            // ---- level 0: row i enters (past the sweep the loads gave zero)
+            const C xv = (CON && x_is_z) ? zq[mpos(u, 3)] : xq[mpos(u, 3)];
+            yr[0][mpos(u, 3)] = xs * xv.x;
+            yi[0][mpos(u, 3)] = xs * xv.y;
+            const C zv = zq[mpos(u, 3)];
+            const uint32_t xo = row_off(qx, i + 3 < nsweep, dead);
+            xq[mpos(u, 3)] = load_c(X, xo, (C*)nullptr);
+            if constexpr (CON) zq[mpos(u, 3)] = load_c(Z, xo, (C*)nullptr);
             // ---- levels 1 .. K: row s = i - l
 #pragma unroll
             for (int l = 1; l <= K; ++l) {
                 const int s = i - l;
                 const int su = mpos(u - l - 1, 3), sm = mpos(u - l, 3), sd = mpos(u - l + 1, 3);
-                const int q = grid_row(s);
-                const bool inrow = s >= 0 && s < nsweep;
+                const int slot = mpos(u - l, U);
                 const T mr = yr[l - 1][sm], mi = yi[l - 1][sm];
                 const T ur_ = yr[l - 1][su], ui_ = yi[l - 1][su];   // row s - 1
                 const T dr_ = yr[l - 1][sd], di_ = yi[l - 1][sd];   // row s + 1
-                const T rr = from_right(mr), ri = from_right(mi);
-                const T lr = from_left(mr), li = from_left(mi);
-                const bool diag = tri && cw == q;
-                // neighbours below and to the left; mirrored on the stored diagonal
-                const T br = diag ? rr : dr_, bi = diag ? ri : di_;
-                const T ar = diag ? ur_ : lr, ai = diag ? ui_ : li;
-                const bool dn = LAY != 0 && (rper || q < rows - 1);
-                const T Jup = pjd[l + 1];
-                const T Jdn = pjd[l];
-                T d = pe[l] + ec;
-                if (LAY != 0) {
-                    int dd = q - cw;
-                    dd = dd < 0 ? -dd : dd;
-                    if (periodic && N - dd < dd) dd = N - dd;
-                    if (dd == want) d += Udt;
-                }
-                T hr = d * mr, hi = d * mi;
-                hr = fma(Jup, ur_, hr);
-                hi = fma(Jup, ui_, hi);
-                hr = fma(Jdn, br, hr);
-                hi = fma(Jdn, bi, hi);
-                hr = fma(jl, ar, hr);
-                hi = fma(jl, ai, hi);
-                hr = fma(jr, rr, hr);
-                hi = fma(jr, ri, hi);
-                // Y_l = cz_l Z + s (-i)(hr + i hi) = cz_l Z + s (hi - i hr)
-                const bool keep = inrow && stored(q);
-                T yr_ = sg * hi, yi_ = -sg * hr;
+                T yr_, yi_, rr = T(0), ri = T(0);
                 if constexpr (CON) {
                     const T cz = static_cast<T>(a.cz[l]);
-                    yr_ = fma(cz, zr[l], yr_);
-                    yi_ = fma(cz, zi[l], yi_);
+                    yr_ = cz * zr[slot];
+                    yi_ = cz * zi[slot];
                 }
-                yr_ = keep ? yr_ : T(0);
-                yi_ = keep ? yi_ : T(0);
+                if constexpr (tri) {
+                    stencil<T, true, CON>(mr, mi, ur_, ui_, dr_, di_, cd[slot], cu[slot], cb[slot], cl[slot],
+                                          cr[slot], yr_, yi_, rr, ri);
+                } else {
+                    const T up = (U == K && l == K) ? sb_last : sb[mpos(u - l - 1, U)];
+                    stencil<T, false, CON>(mr, mi, ur_, ui_, dr_, di_, cd[slot], up, sb[slot], jl, jr, yr_, yi_, rr,
+                                           ri);
+                }
+                if (!CON || l == K) store_c(yr_, yi_, Y[l - 1], so[slot]);
+                if constexpr (CON) {
+                    const C v0 = vq[l - 1][sm], vp = vq[l - 1][sd];
+                    T s0, hb;
+                    contract(mr, mi, dr_, di_, rr, ri, v0.x, v0.y, vp.x, vp.y, s0, hb, rpv[slot]);
+                    rps[slot] += s0;
+                    // rows of the segment only; v holds zeros before it
+                    const double own = (s >= o_lo && s < o_hi) ? 1.0 : 0.0;
+                    site_col = fma(own, (double)s0, site_col);
+                    bond_col = fma(own, (double)hb, bond_col);
+                    // v[l - 1] row s + 3
+                    vq[l - 1][sm] = load_c(V[l - 1], vo[mpos(u - l + 3, U)], (C*)nullptr);
+                }
                 if (l < K) {
                     yr[l][sm] = yr_;
                     yi[l][sm] = yi_;
                 }
-                const bool own = s >= o_lo && s < o_hi;
-                if (!CON || l == K) store_c(yr_, yi_, Y[l - 1], (own && out) ? ro[l + 3] : kPastEnd);
-                if constexpr (CON) {
-                    // Im conj(u) v with u = level l's input, v = v[l - 1], per
-                    // pair in the state's precision, summed in FP64
-                    const C v0 = vq[l - 1][0], vp = vq[l - 1][1];
-                    const T vr = from_right(v0.x), vi = from_right(v0.y);
-                    const bool st = own && out && stored(q);
-                    const T s0 = im_t(mr, mi, v0.x, v0.y);
-                    const T hb = im_t(mr, mi, vr, vi) + im_t(rr, ri, v0.x, v0.y);
-                    site_col += st ? (double)s0 : 0.0;
-                    bond_col += (st && has_bond_c) ? (double)hb : 0.0;
-                    const T vb = im_t(mr, mi, vp.x, vp.y) + im_t(dr_, di_, v0.x, v0.y);
-                    rpv[l] += (st && dn && (!tri || cw >= q + 1)) ? vb : T(0);
-                    rps[l] += (st && !diag) ? s0 : T(0);
-                    // v[l - 1] advances one row
-                    vq[l - 1][0] = vq[l - 1][1];
-                    vq[l - 1][1] = vq[l - 1][2];
-                    vq[l - 1][2] = load_c(V[l - 1], ro[l], (C*)nullptr);
-                }
             }
             if constexpr (CON) {
-                // row i - K is complete (stage K); the stages advance
+                // row i - K is complete; its slot takes row i
                 if (LAY != 0) {
-                    batch[2 * u] = (double)rpv[K];
-                    batch[2 * u + 1] = (double)rps[K];
-                }
-#pragma unroll
-                for (int l = K; l >= 2; --l) {
-                    rpv[l] = rpv[l - 1];
-                    rps[l] = rps[l - 1];
-                }
-                rpv[1] = rps[1] = T(0);
-                if (LAY != 0 && u == 2) {
-                    // rows i - K - 2 .. i - K: lane 8 j ends with the wave's sum of batch[j]
-                    const double t = reduce8(batch, lane);
-                    const int j = lane >> 3;
-                    const int s = i - K - 2 + (j >> 1);
-                    if ((lane & 7) == 0 && j < 6 && s >= o_lo && s < o_hi) {
-                        const int q = grid_row(s);
-                        if (j & 1) gR[q] += f * t;
-                        else gV[q] += f * t;
+                    const bool diag = tri && cw == qi - K;
+                    batch[2 * mpos(u, 3)] = (double)(out ? rpv[mpos(u - K, U)] : T(0));
+                    batch[2 * mpos(u, 3) + 1] = (double)((out && !diag) ? rps[mpos(u - K, U)] : T(0));
+                    if (mpos(u, 3) == 2) {
+                        // lane 8 j ends with the wave's sum of batch[j]
+                        const double t = reduce8(batch, lane);
+                        const int sr = i - K - 2 + j_row;
+                        if (holds_row(sr)) g_row[s_lo + sr] = g_old + f * t;
+                        if (holds_row(sr + 3)) g_old = g_row[s_lo + sr + 3];
                     }
                 }
+                vo[mpos(u + 3, U)] = row_off(qx, i + 3 >= o_lo && i + 3 <= o_hi && i + 3 < nsweep, dead);
             }
+            // ---- row i's coefficients take the slot
+            {
+                const bool live = i < nsweep;
+                const bool stored = inb && (!tri || cw >= qi);
+                int dd = qi - cw;
+                dd = dd < 0 ? -dd : dd;
+                if (periodic && N - dd < dd) dd = N - dd;
+                T d = ge[u] + ec;
+                if (LAY != 0 && dd == want) d += Udt;
+                cd[mpos(u, U)] = (live && stored) ? d : T(0);
+                // the bond to row i + 1: none below the grid or past the sweep
+                const T below = (LAY != 0 && i + 1 < nsweep) ? gj[u] : T(0);
+                if constexpr (tri) {
+                    const bool diag = cw == qi;
+                    cu[mpos(u, U)] = stored ? (diag ? above + jl : above) : T(0);
+                    cb[mpos(u, U)] = (stored && !diag) ? below : T(0);
+                    cl[mpos(u, U)] = (stored && !diag) ? jl : T(0);
+                    cr[mpos(u, U)] = stored ? (diag ? jr + below : jr) : T(0);
+                    above = below;
+                } else {
+                    if (U == K) sb_last = sb[mpos(u, U)];
+                    sb[mpos(u, U)] = below;
+                }
+                so[mpos(u, U)] = row_off(qi, i >= o_lo && i < o_hi, dead | dead_out);
+                if constexpr (CON) {
+                    zr[mpos(u, U)] = zv.x;
+                    zi[mpos(u, U)] = zv.y;
+                    rpv[mpos(u, U)] = rps[mpos(u, U)] = T(0);
+                }
+            }
+            qi = next_row(qi);
+            qx = next_row(qx);
+            __builtin_amdgcn_sched_barrier(0);   // rows interleaved would not fit the registers
         }
     }
     if constexpr (CON) {
         // column parts of the segments, summed in segment order
-        __shared__ double part[2][kSweepSegs][64];
-        part[0][seg][lane] = bond_col;
+        __shared__ double part[2][kSweepSegsMax][64];
+        part[0][seg][lane] = has_bond_c ? bond_col : 0.0;
         part[1][seg][lane] = site_col;
         __syncthreads();
         if (seg == 0 && out) {
             double sb = 0.0, ss = 0.0;
-#pragma unroll
-            for (int k = 0; k < kSweepSegs; ++k) {
+            for (int k = 0; k < segs; ++k) {
                 sb += part[0][k][lane];
                 ss += part[1][k][lane];
             }

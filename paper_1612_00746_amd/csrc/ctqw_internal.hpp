@@ -254,9 +254,10 @@ void obs3_split(int N, int64_t R, Obs3Args* a);
 hipError_t launch_obs3(const Obs3Args& a, int dtype, hipStream_t stream);
 
 // ---------------------------------------------------------------- adjoint
-// Backward passes: a block of kSweepSegs waves splits a band's rows into
-// consecutive segments, one wave each.
+// Backward passes: a block's waves split a band's rows into consecutive
+// segments, one wave each.
 constexpr int kSweepSegs = 4;
+constexpr int kSweepSegsMax = 8;   // batches that leave the device idle
 
 struct AdjWeightArgs {
     const void* psi;
