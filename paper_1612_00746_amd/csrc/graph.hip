@@ -9,17 +9,29 @@
 // tables (plain sums); the optional per-step norms are FP64 either way.
 //
 // Work mapping: one thread per node and group of realisations (four for
-// complex64, one for complex128); nodes
-// along x (coalesced reads of the ELL slots, the couplings, the on-site
-// energies and the state), realisation groups along y, strided over the
-// grid's second dimension.
+// complex64, one for complex128); nodes along the threads (coalesced reads of
+// the ELL slots, the couplings, the on-site energies and the state).  Where
+// the groups fill the eight XCDs about evenly, a group's blocks all go to one
+// XCD: its L2 then fetches that group's previous term once, where blocks
+// dealt in turn have every XCD fetch every realisation.  Otherwise the blocks
+// run along x and the groups, strided, along y.
 // Per node, term and realisation the pass reads the previous term at the
-// node and its neighbours (the neighbours mostly from cache), width
-// couplings and slot indices, the on-site energy and the partial sum, and
-// writes the term and the partial sum: it is HBM-bound.
+// node and its neighbours, width couplings and slot indices and the on-site
+// energy and writes the term.  Only every second term touches the partial sum: the
+// term before it is the node's own value of the source, which is at hand, so
+// the sum takes both in the order of one after the other (the same bits, 32
+// of 136 bytes less in every second term of a complex128 graph of width 8).
+// The step's squared norms are block sums of its last term.
+// Bound by the couplings' traffic.  Two bosons on 15 x 15 nodes (25425 states,
+// width 8), 32 realisations, complex128: 26.3 -> 17.7 us per term (98 MB on
+// average: 5.5 TB/s), with every slot's loads behind the previous slot's branch
+// before; the step's norms, one block per realisation before, 28.8 -> 5.1 us.
+// 24 x 24 nodes, 16 realisations, 127 -> 68 us; one walker on 128 x 128, 256
+// realisations, 92 -> 66 (complex64 46 -> 31).
 #include "graph.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ctqw {
 namespace {
@@ -39,106 +51,160 @@ template <typename T> struct RealsPerThread;
 template <> struct RealsPerThread<float> { static constexpr int value = 4; };
 template <> struct RealsPerThread<double> { static constexpr int value = 1; };
 
-template <typename T>
+// Sum of one double per thread of a block of 256, the same on every run; the
+// result is thread 0's.
+__device__ inline double block_sum(double v, double* part) {
+    const int t = (int)threadIdx.x;
+    part[t] = v;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (t < w) part[t] += part[t + w];
+        __syncthreads();
+    }
+    const double sum = part[0];
+    __syncthreads();
+    return sum;
+}
+
+// NORM: the last term of a step; the block's part of the squared norms goes to a.parts.
+template <typename T, bool NORM>
 __global__ __launch_bounds__(256) void graph_term_kernel(GraphTermArgs a) {
     using C = typename Cplx<T>::type;
     constexpr int Q = RealsPerThread<T>::value;
-    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= a.n) return;
+    constexpr int S = 4;   // slots whose loads are in flight together
+    __shared__ double part[NORM ? 256 : 1];
     const int64_t n = a.n;
     const T* hop = static_cast<const T*>(a.hop);
     const T* onsite = static_cast<const T*>(a.onsite);
     const C* src = static_cast<const C*>(a.src);
     const T cf = static_cast<T>(a.c);
     const int64_t groups = ((int64_t)a.R + Q - 1) / Q;
-    for (int64_t g = blockIdx.y; g < groups; g += gridDim.y) {
+    int32_t bx = (int32_t)blockIdx.x;
+    int64_t g0 = blockIdx.y, step = gridDim.y;
+    if (a.by_xcd) {   // one group per block
+        const uint32_t k = blockIdx.x >> 3;
+        bx = (int32_t)(k % (uint32_t)a.node_blocks);
+        g0 = (int64_t)(k / (uint32_t)a.node_blocks) * 8 + (blockIdx.x & 7);
+        step = groups;
+    }
+    const int64_t i = (int64_t)bx * 256 + threadIdx.x;
+    const bool in = i < n;
+    const int32_t ic = in ? (int32_t)i : 0;   // threads past the end load node 0 and store nothing
+    for (int64_t g = g0; g < groups; g += step) {
         const int64_t r0 = g * Q;
         const int nr = (int)((int64_t)a.R - r0 < Q ? (int64_t)a.R - r0 : Q);
+        // rows of this group's realisations; a missing one repeats the first
+        int64_t row[Q];
         T hr[Q], hi[Q];
+        C x[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            hr[q] = T(0);
-            hi[q] = T(0);
-            if (q < nr) {
-                const C xi = src[(r0 + q) * n + i];
-                const T e = onsite[(r0 + q) * n + i];
-                hr[q] = e * xi.x;
-                hi[q] = e * xi.y;
-            }
+            row[q] = r0 + (q < nr ? q : 0);
+            x[q] = src[row[q] * n + ic];
+            const T e = onsite[row[q] * n + ic];
+            hr[q] = e * x[q].x;
+            hi[q] = e * x[q].y;
         }
-        for (int32_t k = 0; k < a.width; ++k) {
-            const int32_t j = a.nbr[(int64_t)k * n + i];
-            if (j < 0 || j >= a.n) continue;
+        // No branch around the loads: an empty slot reads node i and its sum
+        // is dropped.
+        int32_t k0 = 0;
+        auto slots = [&](auto count) {
+            constexpr int M = decltype(count)::value;
+            int32_t j[M];
+            bool has[M];
+            T c[M][Q];
+            C xj[M][Q];
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                if (q < nr) {
-                    const T c = hop[((r0 + q) * a.width + k) * n + i];
-                    const C xj = src[(r0 + q) * n + j];
-                    hr[q] = fma_r(c, xj.x, hr[q]);
-                    hi[q] = fma_r(c, xj.y, hi[q]);
+            for (int k = 0; k < M; ++k) {
+                j[k] = a.nbr[(int64_t)(k0 + k) * n + ic];
+                has[k] = j[k] >= 0 && j[k] < a.n;
+                j[k] = has[k] ? j[k] : ic;
+            }
+#pragma unroll
+            for (int k = 0; k < M; ++k)
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    c[k][q] = hop[(row[q] * a.width + k0 + k) * n + ic];
+                    xj[k][q] = src[row[q] * n + j[k]];
                 }
-            }
-        }
+#pragma unroll
+            for (int k = 0; k < M; ++k)
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    hr[q] = has[k] ? fma_r(c[k][q], xj[k][q].x, hr[q]) : hr[q];
+                    hi[q] = has[k] ? fma_r(c[k][q], xj[k][q].y, hi[q]) : hi[q];
+                }
+            k0 += M;
+        };
+        while (k0 + S <= a.width) slots(std::integral_constant<int, S>{});
+        while (k0 < a.width) slots(std::integral_constant<int, 1>{});
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            if (q < nr) {
-                const int64_t o = (r0 + q) * n + i;
-                // (-i c) (hr + i hi) = c hi - i c hr
-                C t;
-                t.x = cf * hi[q];
-                t.y = -cf * hr[q];
-                if (a.t_out) static_cast<C*>(a.t_out)[o] = t;
-                const C s = static_cast<const C*>(a.acc_in)[o];
-                C out;
-                out.x = s.x + t.x;
-                out.y = s.y + t.y;
-                static_cast<C*>(a.acc_out)[o] = out;
+            const bool mine = in && q < nr;
+            const int64_t o = row[q] * n + ic;
+            // (-i c) (hr + i hi) = c hi - i c hr
+            C t;
+            t.x = cf * hi[q];
+            t.y = -cf * hr[q];
+            if (a.t_out && mine) static_cast<C*>(a.t_out)[o] = t;
+            double n2 = 0.0;
+            if (a.acc_out && mine) {
+                C s = static_cast<const C*>(a.acc_in)[o];
+                if (a.add_src) {
+                    s.x += x[q].x;
+                    s.y += x[q].y;
+                }
+                s.x += t.x;
+                s.y += t.y;
+                static_cast<C*>(a.acc_out)[o] = s;
+                const double re = s.x, im = s.y;
+                n2 = fma(re, re, im * im);
+            }
+            if constexpr (NORM) {
+                const double sum = block_sum(n2, part);
+                if (threadIdx.x == 0 && q < nr) a.parts[(r0 + q) * a.node_blocks + bx] = sum;
             }
         }
     }
 }
 
-// Squared FP64 norm of each realisation: block r strides over its nodes,
-// then a fixed shared-memory tree, so the result does not depend on timing.
-template <typename T>
-__global__ __launch_bounds__(256) void graph_norm_kernel(const void* psi, int32_t n, double* out) {
-    using C = typename Cplx<T>::type;
+// out[r]: the parts of one realisation, in a fixed order.
+__global__ __launch_bounds__(256) void graph_norm_kernel(const double* parts, int32_t per_real, double* out) {
     __shared__ double part[256];
-    const int64_t r = blockIdx.x;
-    const C* x = static_cast<const C*>(psi) + r * (int64_t)n;
+    const double* x = parts + blockIdx.x * (int64_t)per_real;
     double acc = 0.0;
-    for (int32_t i = (int32_t)threadIdx.x; i < n; i += 256) {
-        const C v = x[i];
-        const double re = v.x, im = v.y;
-        acc = fma(re, re, fma(im, im, acc));
-    }
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[r] = part[0];
+    for (int32_t i = (int32_t)threadIdx.x; i < per_real; i += 256) acc += x[i];
+    const double sum = block_sum(acc, part);
+    if (threadIdx.x == 0) out[blockIdx.x] = sum;
+}
+
+template <typename T>
+hipError_t launch_term(GraphTermArgs a, hipStream_t s) {
+    constexpr int Q = RealsPerThread<T>::value;
+    const int64_t groups = ((int64_t)a.R + Q - 1) / Q;
+    a.node_blocks = (int32_t)(((int64_t)a.n + 255) / 256);
+    // One XCD per group where the fullest XCD has at most a quarter more than
+    // an even share.  Per term and step in turn -> by XCD, two bosons on 15 x
+    // 15, complex128: R = 8 8.5 -> 7.0 us, 14 (share 1.14) 11.9 -> 11.2, 33
+    // (1.21) 23.4 -> 20.5; 12 (1.33) 10.5 -> 11.2, 9 (1.78) 8.9 -> 10.1.
+    const int64_t rounds = (groups + 7) / 8, blocks = rounds * 8 * a.node_blocks;
+    a.by_xcd = rounds * 8 * 4 <= groups * 5 && blocks <= INT32_MAX;
+    const dim3 grid = a.by_xcd ? dim3((unsigned)blocks)
+                               : dim3((unsigned)a.node_blocks, (unsigned)std::min<int64_t>(groups, 65535));
+    if (a.parts) hipLaunchKernelGGL((graph_term_kernel<T, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((graph_term_kernel<T, false>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_graph_norms(const void* psi, int32_t n, int32_t R, double* out, int dtype, hipStream_t s) {
-    if (dtype == 1)
-        hipLaunchKernelGGL(graph_norm_kernel<double>, dim3((unsigned)R), dim3(256), 0, s, psi, n, out);
-    else
-        hipLaunchKernelGGL(graph_norm_kernel<float>, dim3((unsigned)R), dim3(256), 0, s, psi, n, out);
-    return hipGetLastError();
+hipError_t launch_graph_term(const GraphTermArgs& a, int dtype, hipStream_t s) {
+    return dtype == 1 ? launch_term<double>(a, s) : launch_term<float>(a, s);
 }
 
-hipError_t launch_graph_term(const GraphTermArgs& a, int dtype, hipStream_t s) {
-    const int q = dtype == 1 ? RealsPerThread<double>::value : RealsPerThread<float>::value;
-    const int32_t groups = (int32_t)(((int64_t)a.R + q - 1) / q);
-    const dim3 grid((unsigned)((a.n + 255) / 256), (unsigned)std::min<int32_t>(groups, 65535));
-    if (dtype == 1)
-        hipLaunchKernelGGL(graph_term_kernel<double>, grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(graph_term_kernel<float>, grid, dim3(256), 0, s, a);
+hipError_t launch_graph_norms(const double* parts, int32_t n, int32_t R, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(graph_norm_kernel, dim3((unsigned)R), dim3(256), 0, s, parts, (int32_t)(((int64_t)n + 255) / 256),
+                       out);
     return hipGetLastError();
 }
 

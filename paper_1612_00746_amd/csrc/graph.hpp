@@ -14,14 +14,18 @@ struct GraphTermArgs {
     const void* src;         // [R][n] the previous term (or the state)
     void* t_out;             // [R][n] this term, or NULL when no later term needs it
     const void* acc_in;      // [R][n] partial sum before this term
-    void* acc_out;           // [R][n] partial sum after it
+    void* acc_out;           // [R][n] partial sum after it, or NULL: the next term adds this one
+    double* parts;           // [R][ceil(n / 256)] parts of acc_out's squared norms, or NULL
+    int32_t add_src;         // the sum takes the source first (the term that left it out)
     double c;                // dt / j for term j
     int32_t n;
     int32_t width;
     int32_t R;
+    int32_t node_blocks;     // set by the launcher
+    int32_t by_xcd;
 };
 hipError_t launch_graph_term(const GraphTermArgs& a, int dtype, hipStream_t s);
-// out[r] = sum_i |psi[r][i]|^2 in FP64, one block per realisation, fixed summation order.
-hipError_t launch_graph_norms(const void* psi, int32_t n, int32_t R, double* out, int dtype, hipStream_t s);
+// out[r] = the sum of the parts of realisation r, in a fixed order.
+hipError_t launch_graph_norms(const double* parts, int32_t n, int32_t R, double* out, hipStream_t s);
 
 }  // namespace ctqw

@@ -2002,15 +2002,23 @@ ctqw_status ctqw_graph_evolve(int32_t n_nodes, int32_t width, const int32_t* nbr
         for (int32_t j = 1; j <= order; ++j) {
             const bool last = j == order;
             a.t_out = last ? nullptr : T[(j - 1) & 1];
-            // the last term may write the state: it reads only the previous term and the sum
-            a.acc_out = (last && order > 1) ? psi : acc;
+            // every second term adds itself and, first, the one before it, its source
+            a.add_src = j > 1 && (j & 1) == 0;
+            a.acc_out = nullptr;
+            if (last) a.acc_out = order > 1 ? psi : acc;   // it reads only the previous term and the sum
+            else if (a.add_src) a.acc_out = acc;
+            // the last term writes no term: its buffer takes the parts of the norms
+            // (8 ceil(n / 256) R bytes of n R amplitudes)
+            a.parts = last && norms ? static_cast<double*>(T[(j - 1) & 1]) : nullptr;
             a.c = dt / (double)j;
             HIP_TRY(nullptr, launch_graph_term(a, dt_, s));
             a.src = a.t_out;
-            a.acc_in = acc;
+            if (a.acc_out) a.acc_in = acc;
         }
         if (order == 1) HIP_TRY(nullptr, hipMemcpyAsync(psi, acc, bytes, hipMemcpyDeviceToDevice, s));
-        if (norms) HIP_TRY(nullptr, launch_graph_norms(psi, n_nodes, R, norms + step * (int64_t)R, dt_, s));
+        if (norms)
+            HIP_TRY(nullptr, launch_graph_norms(static_cast<const double*>(T[(order - 1) & 1]), n_nodes, R,
+                                                norms + step * (int64_t)R, s));
     }
     return CTQW_OK;
 }
