@@ -96,6 +96,22 @@ __device__ __forceinline__ void stencil_c64_p1(float& hr, float& hi, float d, fl
         : "=&v"(hr), "=&v"(hi)
         : "v"(d), "v"(mr), "v"(mi), "v"(ur), "v"(ui), "v"(vr), "v"(vi), "s"(Ju), "s"(Jd), "v"(jl), "v"(jr));
 }
+// The triangle's form: the bonds above and to the right are per lane (cu, jr).
+__device__ __forceinline__ void stencil_c64_p1_tri(float& hr, float& hi, float d, float mr, float mi, float ur, float ui,
+                                                   float vr, float vi, float cu, float Jd, float jl, float jr) {
+    asm("v_mul_f32 %0, %2, %3\n\t"
+        "v_mul_f32 %1, %2, %4\n\t"
+        "v_fmac_f32 %0, %9, %5\n\t"
+        "v_fmac_f32 %1, %9, %6\n\t"
+        "v_fmac_f32 %0, %10, %7\n\t"
+        "v_fmac_f32 %1, %10, %8\n\t"
+        "v_fmac_f32_dpp %0, %3, %11 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %1, %4, %11 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %0, %3, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f32_dpp %1, %4, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "=&v"(hr), "=&v"(hi)
+        : "v"(d), "v"(mr), "v"(mi), "v"(ur), "v"(ui), "v"(vr), "v"(vi), "v"(cu), "s"(Jd), "v"(jl), "v"(jr));
+}
 // Two columns per lane: column 0's left neighbour and column 1's right
 // neighbour come from the adjacent lanes, the others from this lane.
 __device__ __forceinline__ void stencil_c64_p2(float (&hr)[2], float (&hi)[2], const float (&d)[2], const float (&mr)[2],
@@ -388,6 +404,13 @@ __device__ __forceinline__ void process_item(const StepArgs& a, int home, int la
     T cr[WA][P], ci[WA][P];         // sum of the terms j >= 1 of the rows in flight (KAHAN)
     T dg[WA][P];                    // dt * diagonal of H on the rows in flight
     T ju[WA];                       // dt * bond above each row in flight (uniform)
+    // complex64 triangle: the row's bonds above and to the right per lane,
+    // doubled on the stored diagonal (its mirrored neighbours) and, like dg,
+    // zero where no amplitude is stored: formed once per row, where the levels
+    // would each compare and select.  Two bosons, N = 256, 512 realisations, 7
+    // terms: 159 -> 132 us per step, 173 -> 131 VALU instructions per row.
+    constexpr bool TRIC = TRI && sizeof(T) == 4 && P == 1;   // elsewhere the rings would spill
+    T cu_[TRIC ? WA : 1][P], crt_[TRIC ? WA : 1][P];
     C pre[PF][P];                   // rows being fetched
     C prea[CHUNK ? PF : 1][P];      // chunked pass: their partial sums
     T pj[3], pe[3];                 // bond above and energy of the next rows (uniform)
@@ -403,6 +426,7 @@ __device__ __forceinline__ void process_item(const StepArgs& a, int home, int la
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             ar[w][p] = ai[w][p] = cr[w][p] = ci[w][p] = dg[w][p] = T(0);
+            if constexpr (TRIC) cu_[w][p] = crt_[w][p] = T(0);
         }
     }
     // Grid rows are tracked incrementally: qm_in is the row entering at the
@@ -527,6 +551,14 @@ __device__ __forceinline__ void process_item(const StepArgs& a, int home, int la
                     for (int p = 0; p < P; ++p) {
                         T d0 = er + ec[p];
                         if (colw[p] == t1 || colw[p] == t2) d0 += Udt;
+                        if constexpr (TRIC) {
+                            const bool low = col[p] < qm || (fermi && col[p] == qm);
+                            const bool twice = col[p] == qm;
+                            const T up = ju[u];
+                            cu_[u][p] = low ? T(0) : (twice ? up + up : up);
+                            crt_[u][p] = low ? T(0) : (twice ? jr[p] + jr[p] : jr[p]);
+                            d0 = low ? T(0) : d0;
+                        }
                         dg[u][p] = d0;
                     }
                     qm_in = next_row(qm_in);
@@ -573,6 +605,10 @@ __device__ __forceinline__ void process_item(const StepArgs& a, int home, int la
                                 stencil_c64_p2(hrv, hiv, dg[w], fr[j - 1][sm], fi[j - 1][sm], fr[j - 1][su],
                                                fi[j - 1][su], fr[j - 1][sd], fi[j - 1][sd], Ju, Jd, jl, jr);
                         }
+                    } else if constexpr (TRIC) {
+                        stencil_c64_p1_tri(hrv[0], hiv[0], dg[w][0], fr[j - 1][sm][0], fi[j - 1][sm][0],
+                                           fr[j - 1][su][0], fi[j - 1][su][0], fr[j - 1][sd][0], fi[j - 1][sd][0],
+                                           cu_[w][0], Jd, jl[0], crt_[w][0]);
                     } else {
                         T lr[P], li[P], rr[P], ri[P];
 #pragma unroll
@@ -611,7 +647,7 @@ __device__ __forceinline__ void process_item(const StepArgs& a, int home, int la
                     }
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
-                        const bool low = TRI && zone && (col[p] < qa || (fermi && col[p] == qa));
+                        const bool low = TRI && !TRIC && zone && (col[p] < qa || (fermi && col[p] == qa));
                         const T hr = hrv[p], hi = hiv[p];
                         // A_j = H B_{j-1} (from the imaginary-role array), B_j = H A_{j-1}
                         T pr_ = hi;
