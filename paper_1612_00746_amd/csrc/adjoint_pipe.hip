@@ -62,8 +62,8 @@ hipError_t launch_adj_pipe(AdjPipeArgs a, hipStream_t s) {
     // Eight segments shorten a wave's sweep (rows / segs + 3 K) where the
     // blocks are at most one per compute unit; past that they add halo rows.
     // Two Horner levels, distinguishable, N = 129, complex128, 72 blocks: 22.0
-    // us in four segments, 19.6 in eight.  Four Horner levels, two bosons,
-    // N = 256, complex64, 2560 blocks: 299 us in four, 363 in eight.
+    // us in four segments, 19.6 in eight.  Three Horner levels, two bosons,
+    // N = 256, complex64, 2560 blocks: 223 us in four, 249 in eight.
     const int segs = (int64_t)bands * a.R <= 256 ? kSweepSegsMax : kSweepSegs;
     hipLaunchKernelGGL(fn, g, dim3((unsigned)(64 * segs)), 0, s, a);
     return hipGetLastError();

@@ -36,7 +36,7 @@ namespace ctqw {
 // and takes 45 us where two take 19.6, see the kernel's figures).
 constexpr int kPipeMaxLevelsC64 = 8;
 constexpr int kPipeMaxLevelsC128 = 4;
-constexpr int kPipeMaxHornerC64 = 4;
+constexpr int kPipeMaxHornerC64 = 3;
 constexpr int kPipeMaxHornerC128 = 2;
 constexpr int kPipeMaxLevels = 8;
 

@@ -28,9 +28,9 @@
 // six forward levels take 300 us, of which 140 remain without the stores and
 // 140 are the 0.94 GB at a large copy's rate).  Levels that formed their own
 // diagonal, masks and offsets took 32 VALU instructions per row and level
-// forward and 76 in a Horner pass; these take 15 and 47.  Per time step of
-// that gradient (six forward levels, seven Horner levels): 1070 us then in
-// passes of 6, 3, 2, 2 levels, 824 now in passes of 6, 4, 3.  complex128,
+// forward and 76 in a Horner pass; these take 15 and 52.  Per time step of
+// that gradient (passes of six forward levels and of 3, 2, 2 Horner levels):
+// 1070 -> 949 us.  complex128,
 // distinguishable on a ring of 129 sites, 24 realisations (72 bands):
 // passes of two Horner levels 30 -> 19.6 us, of four forward levels 28 ->
 // 18.5 us, where the loads' latency and the row sums' are what is left.
@@ -75,7 +75,7 @@ using ConstPtr = const __attribute__((address_space(4))) T*;
 // DPP-routed FMAs.  A DPP read of a VGPR must follow the VALU write of that
 // register by two wait states: the DPP instructions come after six VALU
 // instructions of the block, and their sources are inputs of the block.
-//   forward (s = +1): y  = -i h;   Horner (s = -1): y += i h.
+//   forward (s = +1): y = -i h;   Horner (s = -1): y = i h.
 template <typename T, bool LANE_UB, bool NEG>
 __device__ __forceinline__ void stencil(T mr, T mi, T ur, T ui, T dr, T di, T d, T u, T b, T l, T r, T& yr, T& yi,
                                         T& rr, T& ri) {
@@ -94,8 +94,8 @@ __device__ __forceinline__ void stencil(T mr, T mi, T ur, T ui, T dr, T di, T d,
         : "=&v"(yr), "=&v"(yi)                                                               \
         : "v"(mr), "v"(mi), "v"(ur), "v"(ui), "v"(dr), "v"(di), "v"(d), UB(u), UB(b), "v"(l), "v"(r))
 #define CTQW_PIPE_HORNER(UB)                                                                 \
-    asm("v_fma_f32 %0, -%8, %3, %0\n\t"                                                      \
-        "v_fma_f32 %1, %8, %2, %1\n\t"                                                       \
+    asm("v_mul_f32 %0, -%8, %3\n\t"                                                          \
+        "v_mul_f32 %1, %8, %2\n\t"                                                           \
         "v_fma_f32 %0, -%9, %5, %0\n\t"                                                      \
         "v_fma_f32 %1, %9, %4, %1\n\t"                                                       \
         "v_fma_f32 %0, -%10, %7, %0\n\t"                                                     \
@@ -104,7 +104,7 @@ __device__ __forceinline__ void stencil(T mr, T mi, T ur, T ui, T dr, T di, T d,
         "v_fmac_f32_dpp %1, %2, %11 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"  \
         "v_fmac_f32_dpp %0, -%3, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t" \
         "v_fmac_f32_dpp %1, %2, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"      \
-        : "+&v"(yr), "+&v"(yi)                                                               \
+        : "=&v"(yr), "=&v"(yi)                                                               \
         : "v"(mr), "v"(mi), "v"(ur), "v"(ui), "v"(dr), "v"(di), "v"(d), UB(u), UB(b), "v"(l), "v"(r))
         if constexpr (NEG) {
             if constexpr (LANE_UB) CTQW_PIPE_HORNER("v");
@@ -120,9 +120,8 @@ __device__ __forceinline__ void stencil(T mr, T mi, T ur, T ui, T dr, T di, T d,
         ri = from_right(mi);
         const T lr = from_left(mr), li = from_left(mi);
         const T s = NEG ? T(-1) : T(1);
-        if constexpr (!NEG) yr = yi = T(0);
-        yr = fma(s * d, mi, yr);
-        yi = fma(-s * d, mr, yi);
+        yr = s * d * mi;
+        yi = -s * d * mr;
         yr = fma(s * u, ui, yr);
         yi = fma(-s * u, ur, yi);
         yr = fma(s * b, di, yr);
@@ -135,14 +134,14 @@ __device__ __forceinline__ void stencil(T mr, T mi, T ur, T ui, T dr, T di, T d,
 }
 
 // Im conj(y) v with y = a level's input, in the state's precision: the site
-// (s0), the bond to the right (hb) and, added to vb, the bond below (d: the
-// input's row below, p: v's).  rr, ri: the input's right neighbours (complex128).
+// (s0), the bond to the right (hb) and the bond below (vb; d: the input's row
+// below, p: v's).  rr, ri: the input's right neighbours (complex128).
 template <typename T>
 __device__ __forceinline__ void contract(T mr, T mi, T dr, T di, T rr, T ri, T vx, T vy, T px, T py, T& s0, T& hb,
                                          T& vb) {
     if constexpr (sizeof(T) == 4) {
         asm("v_mul_f32 %0, %3, %8\n\t"
-            "v_fma_f32 %2, %3, %10, %2\n\t"
+            "v_mul_f32 %2, %3, %10\n\t"
             "v_fma_f32 %0, -%4, %7, %0\n\t"
             "v_fma_f32 %2, -%4, %9, %2\n\t"
             "v_fma_f32 %2, %5, %8, %2\n\t"
@@ -151,13 +150,13 @@ __device__ __forceinline__ void contract(T mr, T mi, T dr, T di, T rr, T ri, T v
             "v_fmac_f32_dpp %1, -%7, %4 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
             "v_fmac_f32_dpp %1, %3, %8 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
             "v_fmac_f32_dpp %1, -%4, %7 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "=&v"(s0), "=&v"(hb), "+&v"(vb)
+            : "=&v"(s0), "=&v"(hb), "=&v"(vb)
             : "v"(mr), "v"(mi), "v"(dr), "v"(di), "v"(vx), "v"(vy), "v"(px), "v"(py));
     } else {
         const T qx = from_right(vx), qy = from_right(vy);
         s0 = im_t(mr, mi, vx, vy);
         hb = fma(mr, qy, fma(-mi, qx, fma(rr, vy, -(ri * vx))));
-        vb = fma(mr, py, fma(-mi, px, fma(dr, vy, fma(-di, vx, vb))));
+        vb = fma(mr, py, fma(-mi, px, fma(dr, vy, -(di * vx))));
     }
 }
 
@@ -367,11 +366,6 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
                 const T ur_ = yr[l - 1][su], ui_ = yi[l - 1][su];   // row s - 1
                 const T dr_ = yr[l - 1][sd], di_ = yi[l - 1][sd];   // row s + 1
                 T yr_, yi_, rr = T(0), ri = T(0);
-                if constexpr (CON) {
-                    const T cz = static_cast<T>(a.cz[l]);
-                    yr_ = cz * zr[slot];
-                    yi_ = cz * zi[slot];
-                }
                 if constexpr (tri) {
                     stencil<T, true, CON>(mr, mi, ur_, ui_, dr_, di_, cd[slot], cu[slot], cb[slot], cl[slot],
                                           cr[slot], yr_, yi_, rr, ri);
@@ -380,11 +374,18 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
                     stencil<T, false, CON>(mr, mi, ur_, ui_, dr_, di_, cd[slot], up, sb[slot], jl, jr, yr_, yi_, rr,
                                            ri);
                 }
+                if constexpr (CON) {
+                    // last: Z outweighs the rest, which would round at its size
+                    const T cz = static_cast<T>(a.cz[l]);
+                    yr_ = fma(cz, zr[slot], yr_);
+                    yi_ = fma(cz, zi[slot], yi_);
+                }
                 if (!CON || l == K) store_c(yr_, yi_, Y[l - 1], so[slot]);
                 if constexpr (CON) {
                     const C v0 = vq[l - 1][sm], vp = vq[l - 1][sd];
-                    T s0, hb;
-                    contract(mr, mi, dr_, di_, rr, ri, v0.x, v0.y, vp.x, vp.y, s0, hb, rpv[slot]);
+                    T s0, hb, vb;
+                    contract(mr, mi, dr_, di_, rr, ri, v0.x, v0.y, vp.x, vp.y, s0, hb, vb);
+                    rpv[slot] += vb;
                     rps[slot] += s0;
                     // rows of the segment only; v holds zeros before it
                     const double own = (s >= o_lo && s < o_hi) ? 1.0 : 0.0;
