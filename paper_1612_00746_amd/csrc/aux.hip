@@ -72,28 +72,35 @@ __global__ void finalize_kernel(FinalizeArgs a) {
     const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (r >= a.R) return;   // wave-uniform
-    double s = 0.0, t = 0.0;
-    for (int32_t k = a.item_first[r] + lane; k < a.item_first[r + 1]; k += 64) {
-        s += a.norm_part[k];
-        t += a.tail_part[k];
-    }
+    double s = 0.0, t = 0.0, err2 = 0.0;
+    const int32_t k0 = a.item_first[r], k1 = a.item_first[r + 1];
+    const double tf = a.use_max ? a.reals[r].tail_factor_max : a.reals[r].tail_factor;
+    int flags = 0, alarms = 0;
+    for (int m = 0; m < a.slots; ++m) {
+        s = t = 0.0;
+        for (int32_t k = k0 + lane; k < k1; k += 64) {
+            s += a.norm_part[m * a.slot_stride + k];
+            t += a.tail_part[m * a.slot_stride + k];
+        }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        s += __shfl_xor(s, off, 64);
-        t += __shfl_xor(t, off, 64);
+        for (int off = 32; off >= 1; off >>= 1) {
+            s += __shfl_xor(s, off, 64);
+            t += __shfl_xor(t, off, 64);
+        }
+        err2 = t * tf * tf;
+        int flag = 0;
+        if (a.tol2 > 0.0 && !(err2 <= a.tol2 * s)) flag |= 1;
+        if (!isfinite(s) || !isfinite(t)) flag |= 2;
+        if (a.norm_alarm > 0.0 && !(fabs(sqrt(s) - 1.0) <= a.norm_alarm)) flag |= 2;
+        flags |= flag;
+        alarms += flag ? 1 : 0;
     }
     if (lane != 0) return;
-    const double tf = a.use_max ? a.reals[r].tail_factor_max : a.reals[r].tail_factor;
-    const double err2 = t * tf * tf;
     a.norm2[r] = s;
     a.tail2[r] = err2;
-    int flag = 0;
-    if (a.tol2 > 0.0 && !(err2 <= a.tol2 * s)) flag |= 1;
-    if (!isfinite(s) || !isfinite(t)) flag |= 2;
-    if (a.norm_alarm > 0.0 && !(fabs(sqrt(s) - 1.0) <= a.norm_alarm)) flag |= 2;
-    if (flag) {
-        atomicOr(&a.status[0], flag);
-        atomicAdd(&a.status[1], 1);
+    if (flags) {
+        atomicOr(&a.status[0], flags);
+        atomicAdd(&a.status[1], alarms);
     }
     if (a.renormalize && s > 0.0 && isfinite(s)) a.scale[r] = 1.0 / sqrt(s);
 }

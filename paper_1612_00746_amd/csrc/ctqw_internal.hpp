@@ -127,6 +127,8 @@ struct FinalizeArgs {
     double norm_alarm;
     int renormalize;
     int use_max;                 // the step ran every realisation at the batch's largest order
+    int slots;                   // steps to take, in order
+    int64_t slot_stride;         // partials of one
 };
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t stream);
 
