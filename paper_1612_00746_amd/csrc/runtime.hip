@@ -543,9 +543,16 @@ ctqw_status build_tables(ctqw_plan* p) {
                                 : p->launch.row_segments;
         if (!chunk && pr.m == 2 && seg_cap > 1) {
             const bool periodic = pr.boundary == CTQW_PERIODIC;
-            const int64_t want = p->launch.row_segments == 0
-                                     ? (kSplitTarget + (int64_t)items.size() - 1) / (int64_t)items.size()
-                                     : seg_cap;
+            // Full-grid complex128 waves have a SIMD to themselves, and a few items
+            // past one per SIMD take a second round: round down (N = 704, order 7:
+            // R = 4 74 us per step rounding up, 45 down; R = 16 158 / 96; N = 256,
+            // order 9, R = 40 99 / 68).  A triangle's short bands split less, so
+            // its items stay below the target (N = 256, R = 60 106 up, 135 down),
+            // and complex64 has two waves per SIMD.
+            const int64_t n = (int64_t)items.size();
+            const bool down = dtype == 1 && pr.statistics == CTQW_DISTINGUISHABLE && 2 * n <= kSplitTarget;
+            const int64_t fit = down ? kSplitTarget / n : (kSplitTarget + n - 1) / n;
+            const int64_t want = p->launch.row_segments == 0 ? fit : seg_cap;
             const int S = (int)std::min<int64_t>(seg_cap, want);
             std::vector<ItemDev> split;
             split.reserve(items.size() * S);
