@@ -121,6 +121,7 @@ struct ctqw_plan {
     bool more_steps = false;         // set while a loop of steps has another to enqueue
     int levels = 0;                  // Taylor terms per step (the batch's order)
     int chunk = 0;                   // terms per pass of a chunked step (0: fused)
+    int cols = 1;                    // columns per lane of its steps
     ctqw_launch launch{};
     Layout lay;
     bool tables_dirty = true;
@@ -425,11 +426,19 @@ bool make_bands(const ctqw_problem& pr, int r, int N, int h, int W, int align, b
 
 ctqw_status build_tables(ctqw_plan* p) {
     const ctqw_problem& pr = p->prob;
-    const int P = p->launch.cols_per_lane;
-    const int W = 64 * P;
+    int P = p->launch.cols_per_lane;
     int maxn = 0;
     for (int64_t r = 0; r < pr.R; ++r) maxn = std::max(maxn, p->order[r]);
     const int dtype = pr.dtype == CTQW_C128 ? 1 : 0;
+    // Orders that only one column per lane is compiled for run there in one
+    // pass, whatever the request (passes of a few terms move the state once
+    // each, and their bands are not split).  us per step at N = 300, chunked ->
+    // one pass: full grid complex128 order 12, R = 1 449 -> 58, 60 498 -> 147,
+    // 400 1424 -> 752; complex64 order 10, R = 800 1251 -> 522; bosons complex64
+    // order 10, R = 1000 1265 -> 729, complex128 order 9, R = 600 1434 -> 754,
+    // order 12 the one tie (1436 / 1461; R = 60 622 -> 235).
+    if (pr.m != 3 && step_levels_bucket(dtype, P, maxn) < 0 && step_levels_bucket(dtype, 1, maxn) >= 0) P = 1;
+    const int W = 64 * P;
     const int fused = pr.m == 3 ? maxn : step_levels_bucket(dtype, P, maxn);
     // chunked passes when the order has no fused pipeline, or on request
     const int chunk = (pr.m != 3 && (fused < 0 || p->launch.chunked)) ? chunk_depth(dtype) : 0;
@@ -694,6 +703,7 @@ ctqw_status build_tables(ctqw_plan* p) {
     p->item_order.swap(ord);
     p->levels = levels;
     p->chunk = chunk;
+    p->cols = chunk ? 1 : P;
 
     // workspace layout
     Layout L;
@@ -863,7 +873,7 @@ StepConfig step_config(ctqw_plan* p) {
     c.dtype = p->prob.dtype == CTQW_C128 ? 1 : 0;
     c.kahan = (c.dtype == 0 && p->prob.accumulation == CTQW_ACC_KAHAN) ? 1 : 0;
     c.triangle = (p->prob.m == 2 && p->prob.statistics != CTQW_DISTINGUISHABLE) ? 1 : 0;
-    c.cols_per_lane = p->chunk ? 1 : p->launch.cols_per_lane;
+    c.cols_per_lane = p->cols;
     c.levels = p->chunk ? p->chunk : p->levels;
     c.waves_per_block = p->launch.waves_per_block;
     c.persistent = p->launch.persistent;
