@@ -1252,6 +1252,30 @@ ctqw_status enqueue_step_loop(ctqw_plan* p, int64_t count) {
     return st;
 }
 
+// `len` steps whose intermediate states go to seg, seg + stride, ... and the
+// last to the state buffer.
+ctqw_status enqueue_stored_steps(ctqw_plan* p, int64_t len, uint8_t* seg, int64_t stride) {
+    ctqw_status st = CTQW_OK;
+    const void* in = p->psi[p->cur];
+    p->part_slot = 0;
+    for (int64_t j = 0; j < len && st == CTQW_OK; ++j) {
+        p->more_steps = j + 1 < len;
+        void* out = p->more_steps ? static_cast<void*>(seg + j * stride) : p->psi[1 - p->cur];
+        if (p->timing) st = record_event(p, 0);
+        if (st == CTQW_OK) st = enqueue_step_kernels(p, in, out);
+        if (st == CTQW_OK && p->timing) st = record_event(p, 1);
+        if (st == CTQW_OK) st = enqueue_finalize(p);
+        in = out;
+    }
+    p->more_steps = false;
+    p->part_slot = 0;
+    if (st != CTQW_OK) return st;
+    p->cur = 1 - p->cur;
+    p->steps_done += len;
+    p->have_step_stats = true;
+    return CTQW_OK;
+}
+
 // Advance `count` steps.  With use_graph the sequence of (step, finalize)
 // launches is captured once per (steps, starting buffer) on a private
 // capture stream and the executable graph is replayed on the bound stream.
@@ -2665,7 +2689,13 @@ ctqw_status ctqw_forward_ckpt(ctqw_plan* p, int64_t n_steps, int64_t ckpt_every,
             HIP_TRY(p, launch_copy(G + g.ckpt + (k / C) * g.S, p->psi[p->cur], bytes, s));
         const int64_t run = std::min(C, n_steps - k);
         p->one_depth = true;
-        st = resident ? enqueue_resident_steps(p, rs, run) : enqueue_step_loop(p, run);
+        // the backward pass starts with the newest segment: its states are kept
+        // where it would recompute them: 15 of the 93 steps of a gradient of 48
+        // steps with checkpoints every 16 (512 x two bosons, N = 256, 59.4 ->
+        // 57.4 ms).  On chip a step costs too little to be worth its store.
+        if (resident) st = enqueue_resident_steps(p, rs, run);
+        else if (k + run == n_steps) st = enqueue_stored_steps(p, run, G + g.seg, g.S);
+        else st = enqueue_step_loop(p, run);
         p->one_depth = false;
         if (st != CTQW_OK) return st;
         k += run;
@@ -2767,7 +2797,8 @@ ctqw_status ctqw_backward(ctqw_plan* p, int32_t kind, const double* site_w, void
             p->one_depth = false;
             if (st != CTQW_OK) return st;
         }
-        for (int64_t k = 1; k < len && !resident; ++k)
+        const bool kept = sg == g.n_ckpt - 1;   // by the forward run
+        for (int64_t k = 1; k < len && !resident && !kept; ++k)
             if ((st = enqueue_step_io(p, segp[k - 1], const_cast<void*>(segp[k]))) != CTQW_OK) return st;
         for (int64_t k = len - 1; k >= 0; --k) {
             const void* lam = state(g.lam, lc);
