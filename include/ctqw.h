@@ -508,9 +508,9 @@ ctqw_status ctqw_work_items(const ctqw_plan* plan, int64_t* items, int64_t* wave
  * sum_r dL/dJ^r_i; grad_J [n_bonds(N)] and grad_eps [N] return these, the
  * exact derivatives of the discrete (truncated-Taylor) map, computed by a
  * hand-written adjoint: the forward run keeps the state every ckpt_every
- * steps, each segment but the newest (whose
- * states the forward run may keep) is recomputed from its checkpoint, and the adjoint of
- * every step applies p(A)^dagger with A = -i dt H by a Horner recursion
+ * steps, each segment but the newest (whose states the forward run may
+ * keep) is recomputed from its checkpoint, and the adjoint of every step
+ * applies p(A)^dagger with A = -i dt H by a Horner recursion
  * (the same stencil with dt -> -dt) while FP64 kernels contract the bond
  * and site operators.  All realisations must share one lattice size, whose
  * state is under 2^31 bytes (two particles: N <= 16383 complex64, 11585

@@ -15,12 +15,6 @@ __device__ __forceinline__ double from_right(double x) { return __builtin_amdgcn
 __device__ __forceinline__ float from_left(float x) { return __builtin_amdgcn_update_dpp(0.0f, x, 0x138, 0xF, 0xF, true); }
 __device__ __forceinline__ double from_left(double x) { return __builtin_amdgcn_update_dpp(0.0, x, 0x138, 0xF, 0xF, true); }
 
-// Im(conj(u) v) in FP64.
-template <typename T>
-__device__ __forceinline__ double im_uv(T ur, T ui, T vr, T vi) {
-    return (double)ur * (double)vi - (double)ui * (double)vr;
-}
-
 // Im(conj(u) v) in the state's precision.
 template <typename T>
 __device__ __forceinline__ T im_t(T ur, T ui, T vr, T vi) {

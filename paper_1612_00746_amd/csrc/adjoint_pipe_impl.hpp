@@ -30,10 +30,10 @@
 // diagonal, masks and offsets took 32 VALU instructions per row and level
 // forward and 76 in a Horner pass; these take 15 and 52.  Per time step of
 // that gradient (passes of six forward levels and of 3, 2, 2 Horner levels):
-// 1070 -> 949 us.  complex128,
-// distinguishable on a ring of 129 sites, 24 realisations (72 bands):
-// passes of two Horner levels 30 -> 19.6 us, of four forward levels 28 ->
-// 18.5 us, where the loads' latency and the row sums' are what is left.
+// 1070 -> 949 us.  complex128, distinguishable on a ring of 129 sites, 24
+// realisations (72 bands): passes of two Horner levels 30 -> 19.6 us, of four
+// forward levels 28 -> 18.5 us, where latency is what is left.
+//
 // Contractions.  Full grid (distinguishable particles; one particle is the
 // one-row case): the column parts of bond c and site c are sums over the
 // rows, kept per lane; the row parts of bond q and site q are sums over the
