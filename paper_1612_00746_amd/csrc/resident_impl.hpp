@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
     // One level, in place: t <- (dt H) t; the sum takes the new vector with
     // the factor (-i)^j / j!: ODD levels swap the parts.  Rows 1 .. S - 1
     // first, then row 0: the neighbouring waves' rows are needed last.
-    auto level = [&](auto odd, T c, bool last, T& tail) {
+    auto level = [&](auto odd, T c, bool last, double& tail) {
         constexpr bool ODD = decltype(odd)::value;
         const C* base = pub + buf * slots * 64 * P;
         T lr[P], li[P], hr[P], hi[P];
@@ -471,10 +471,14 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 const int k = kb + s;
-                const T w = k < K ? (TRI && k != 0 && 2 * k != N ? T(2) : T(1)) : T(0);
+                // in FP64: the squares of a deep last term leave FP32's range
+                // before the 1/n! that brings them back is applied
+                const double w = TRI && k != 0 && 2 * k != N ? 2.0 : 1.0;
 #pragma unroll
-                for (int p = 0; p < P; ++p)
-                    if (k < K) tail = fma_t(w, fma_t(tr[s][p], tr[s][p], ti[s][p] * ti[s][p]), tail);
+                for (int p = 0; p < P; ++p) {
+                    const double x = tr[s][p], y = ti[s][p];
+                    if (k < K) tail = __builtin_fma(w, __builtin_fma(x, x, y * y), tail);
+                }
             }
         }
     };
@@ -508,7 +512,7 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
                     ai[s][p] = ti[s][p];
                 }
             }
-        T tail = T(0);
+        double tail = 0.0;
         T sgn = T(1);
         T c1 = static_cast<T>(a.coef[1]), c2 = static_cast<T>(a.coef[2]);
         for (int j = 1; j <= n; j += 2) {
@@ -573,7 +577,7 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
             }
         }
         nrm = wave_sum_last(nrm);
-        const double tl = wave_sum_last((double)tail);
+        const double tl = wave_sum_last(tail);
         double* pp = part + ppar * 2 * W;
         if (lane == 63) {
             pp[2 * wv] = nrm;
