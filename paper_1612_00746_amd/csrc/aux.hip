@@ -147,11 +147,18 @@ hipError_t launch_copy(void* dst, const void* src, int64_t bytes, hipStream_t st
     if (bytes <= 0) return hipSuccess;
     if (bytes % 4 || ((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) & 15))
         return hipErrorInvalidValue;
-    const int64_t n = bytes / 16, blocks = n / 256 + 1;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, static_cast<const f32x4*>(src),
-                       static_cast<f32x4*>(dst), n, (int)(bytes % 16) / 4);
-    return hipGetLastError();
+    const int64_t n = bytes / 16;
+    const f32x4* from = static_cast<const f32x4*>(src);
+    f32x4* to = static_cast<f32x4*>(dst);
+    // a launch takes fewer than 2^32 threads along x: pieces of 16 GiB
+    constexpr int64_t kPiece = int64_t(1) << 30;
+    for (int64_t i = 0;; i += kPiece) {
+        const int64_t m = std::min(n - i, kPiece);
+        const bool last = i + m == n;
+        hipLaunchKernelGGL(copy_kernel, dim3((unsigned)(m / 256 + 1)), dim3(256), 0, stream, from + i, to + i, m,
+                           last ? (int)(bytes % 16) / 4 : 0);
+        if (last) return hipGetLastError();
+    }
 }
 
 hipError_t launch_init(const InitArgs& a, hipStream_t stream) {

@@ -1,0 +1,118 @@
+"""Launch grids of the largest batches, without a device: a launch takes fewer
+than 2^32 threads along x.  A small program that defines the runtime's launch
+calls itself (so that the library's go there) records the grids that the
+launchers ask for; nothing runs, and no pointer is followed.
+
+* copies of states: 64 GiB and more go in pieces that cover every byte once."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_1612_00746_amd")
+
+PROGRAM = r"""
+#include "ctqw_internal.hpp"
+#include "adjoint_pipe.hpp"
+#include "graph.hpp"
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+namespace { dim3 g_grid, g_block; size_t g_lds; hipStream_t g_stream; bool g_copy; }
+
+extern "C" {
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+    g_grid = grid; g_block = block; g_lds = lds; g_stream = stream;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* stream) {
+    *grid = g_grid; *block = g_block; *lds = g_lds; *stream = g_stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+    std::printf("launch %u %u %u %u", grid.x, grid.y, grid.z, block.x);
+    if (g_copy)   // source, destination, 16-byte elements, words after them
+        std::printf(" %llu %llu %lld %d", (unsigned long long)*(void**)args[0], (unsigned long long)*(void**)args[1],
+                    (long long)*(int64_t*)args[2], *(int*)args[3]);
+    std::printf("\n");
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+}
+
+int main(int argc, char** argv) {
+    using namespace ctqw;
+    hipError_t e = hipErrorInvalidValue;
+    if (!std::strcmp(argv[1], "copy")) {
+        g_copy = true;
+        e = launch_copy((void*)(1ull << 40), (const void*)(1ull << 44), std::atoll(argv[2]), nullptr);
+    } else if (!std::strcmp(argv[1], "adjoint")) {
+        AdjPipeArgs a{};
+        double x = 0;
+        a.x = &x;
+        a.sign = 1;
+        a.y[0] = &x;
+        a.R = std::atoll(argv[2]);
+        a.max_n = std::atoi(argv[3]);
+        a.nb = (a.max_n + pipe_band_width(1) - 1) / pipe_band_width(1);
+        a.levels = 1;
+        e = launch_adj_pipe(a, nullptr);
+        std::printf("bands %d\n", a.nb);
+    } else if (!std::strcmp(argv[1], "graph")) {
+        GraphTermArgs a{};
+        a.n = std::atoi(argv[2]);
+        a.R = std::atoi(argv[3]);
+        a.width = 1;
+        e = launch_graph_term(a, 1, nullptr);
+    }
+    std::printf("status %d\n", (int)e);
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    cc = next((c for c in (os.environ.get("HIPCC"), shutil.which("hipcc"), "/opt/rocm/bin/hipcc")
+               if c and os.path.exists(c)), None)
+    if cc is None or not os.path.exists(os.path.join(PKG, "libctqw.so")):
+        pytest.skip("needs hipcc and the built library")
+    d = tmp_path_factory.mktemp("launches")
+    src, exe = str(d / "launches.hip"), str(d / "launches")
+    with open(src, "w") as f:
+        f.write(PROGRAM)
+    subprocess.run([cc, "--offload-host-only", "-std=c++17", "-w", "-I" + os.path.join(PKG, "csrc"),
+                    "-I" + os.path.join(ROOT, "include"), src, "-o", exe, "-rdynamic", "-L" + PKG, "-l:libctqw.so",
+                    "-Wl,-rpath," + PKG], check=True)
+
+    def run(*args):
+        out = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True, timeout=60).stdout
+        lines = [l.split() for l in out.splitlines()]
+        grids = [tuple(map(int, l[1:])) for l in lines if l[0] == "launch"]
+        rest = {l[0]: int(l[1]) for l in lines if l[0] != "launch"}
+        return grids, rest
+    return run
+
+
+def assert_launchable(g):
+    assert g[0] * g[3] < 2 ** 32 and 1 <= g[1] <= 65535 and 1 <= g[2] <= 65535, g
+
+
+@pytest.mark.parametrize("size", [4, 12, 16, 4096, 2 ** 34 - 8, 2 ** 34, 2 ** 34 + 24, 2 ** 36 - 16, 2 ** 36, 2 ** 37 + 8])
+def test_copies_are_launchable_and_cover_every_byte(recorder, size):
+    grids, rest = recorder("copy", size)
+    assert rest["status"] == 0 and grids
+    at = 0
+    for k, g in enumerate(grids):
+        assert_launchable(g)
+        dst_src, elements, words = (g[5], g[4]), g[6], g[7]
+        assert dst_src == (2 ** 40 + at, 2 ** 44 + at)
+        assert g[0] * g[3] > elements      # a thread for each, and one for the words after them
+        assert words == 0 or k == len(grids) - 1
+        at += 16 * elements + 4 * words
+    assert at == size
