@@ -36,7 +36,7 @@ PipeFn pick(const AdjPipeArgs& a) {
 
 static_assert(kSweepSegs == 4 && kSweepSegsMax == 8, "the kernel splits rows by shifts");
 
-hipError_t launch_adj_pipe(AdjPipeArgs a, hipStream_t s) {
+hipError_t launch_adj_pipe(const AdjPipeArgs& a, hipStream_t s) {
     if (a.R < 1 || a.R > 65535 || a.nb < 1 || a.nb > 65535) return hipErrorInvalidValue;
     if (a.levels < 1 || a.levels > pipe_max_levels(a.dtype, a.contract != 0) || a.layout < 0 || a.layout > 2)
         return hipErrorInvalidValue;
@@ -55,10 +55,11 @@ hipError_t launch_adj_pipe(AdjPipeArgs a, hipStream_t s) {
     // bands of the largest chain; a contracting pass has a row-part slot for each
     const int W = pipe_band_width(a.levels);
     const int bands = (a.max_n + W - 1) / W;
-    if (a.max_n < 1 || (a.R + 7) / 8 * 8 * bands > INT32_MAX || (a.contract && bands > a.nb)) return hipErrorInvalidValue;
+    if (a.max_n < 1 || (a.contract && bands > a.nb)) return hipErrorInvalidValue;
     if (a.max_n >= 1 << 28) return hipErrorInvalidValue;
-    a.bands = bands;
-    const dim3 g((unsigned)((a.R + 7) / 8 * 8 * bands));
+    // eight realisations along x, whose threads a launch keeps below 2^32 (8
+    // bands x 512; R / 8 of them along y)
+    const dim3 g((unsigned)(8 * bands), (unsigned)((a.R + 7) / 8));
     // Eight segments shorten a wave's sweep (rows / segs + 3 K) where the
     // blocks are at most one per compute unit; past that they add halo rows.
     // Two Horner levels, distinguishable, N = 129, complex128, 72 blocks: 22.0

@@ -60,7 +60,6 @@ struct AdjPipeArgs {
     int64_t R;
     int nb;                             // band slots per realisation in gV / gR
     int max_n;                          // largest chain of the batch
-    int bands;                          // its bands (set by the launcher)
     int row_stride;
     int levels;                         // K
     int dtype;
@@ -76,6 +75,6 @@ inline int pipe_max_levels(int dtype, bool contract) {
     return dtype == 1 ? kPipeMaxLevelsC128 : kPipeMaxLevelsC64;
 }
 
-hipError_t launch_adj_pipe(AdjPipeArgs a, hipStream_t stream);
+hipError_t launch_adj_pipe(const AdjPipeArgs& a, hipStream_t stream);
 
 }  // namespace ctqw

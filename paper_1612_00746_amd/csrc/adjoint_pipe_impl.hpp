@@ -174,9 +174,8 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
     // Consecutive blocks go to the XCDs in turn: a realisation's bands are
     // given to one XCD, whose L2 then holds the halo columns and the lines
     // that two bands share.
-    const int k8 = blockIdx.x >> 3;
-    const int r = (k8 / a.bands) * 8 + (blockIdx.x & 7);
-    const int w = k8 % a.bands;
+    const int r = (int)blockIdx.y * 8 + (blockIdx.x & 7);
+    const int w = blockIdx.x >> 3;
     if (r >= a.R) return;   // whole block, before the barrier
     const RealDev rd = a.reals[r];
     const int N = rd.N, rows = LAY == 0 ? 1 : rd.rows;

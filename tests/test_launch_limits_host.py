@@ -3,7 +3,8 @@ than 2^32 threads along x.  A small program that defines the runtime's launch
 calls itself (so that the library's go there) records the grids that the
 launchers ask for; nothing runs, and no pointer is followed.
 
-* copies of states: 64 GiB and more go in pieces that cover every byte once."""
+* copies of states: 64 GiB and more go in pieces that cover every byte once;
+* adjoint passes: 65535 chains of 32768 nodes."""
 
 import os
 import shutil
@@ -116,3 +117,12 @@ def test_copies_are_launchable_and_cover_every_byte(recorder, size):
         assert words == 0 or k == len(grids) - 1
         at += 16 * elements + 4 * words
     assert at == size
+
+
+def test_adjoint_passes_of_the_largest_batches(recorder):
+    for R, n in ((65535, 32768), (65535, 15000), (9, 100)):
+        grids, rest = recorder("adjoint", R, n)
+        assert rest["status"] == 0 and len(grids) == 1
+        assert_launchable(grids[0])
+        # whole groups of eight realisations, every band of each
+        assert grids[0][0] * grids[0][1] == (R + 7) // 8 * 8 * rest["bands"]
