@@ -188,7 +188,8 @@ hipError_t launch_term(GraphTermArgs a, hipStream_t s) {
     // 15, complex128: R = 8 8.5 -> 7.0 us, 14 (share 1.14) 11.9 -> 11.2, 33
     // (1.21) 23.4 -> 20.5; 12 (1.33) 10.5 -> 11.2, 9 (1.78) 8.9 -> 10.1.
     const int64_t rounds = (groups + 7) / 8, blocks = rounds * 8 * a.node_blocks;
-    a.by_xcd = rounds * 8 * 4 <= groups * 5 && blocks <= INT32_MAX;
+    // (A launch takes fewer than 2^32 threads along x.)
+    a.by_xcd = rounds * 8 * 4 <= groups * 5 && blocks < int64_t(1) << 24;
     const dim3 grid = a.by_xcd ? dim3((unsigned)blocks)
                                : dim3((unsigned)a.node_blocks, (unsigned)std::min<int64_t>(groups, 65535));
     if (a.parts) hipLaunchKernelGGL((graph_term_kernel<T, true>), grid, dim3(256), 0, s, a);

@@ -65,7 +65,9 @@ bool resident_shape(int layout, int dtype, int kahan, int max_N, int max_order, 
 
 hipError_t launch_resident(const ResidentShape& s, const ResidentArgs& a, int64_t R, hipStream_t stream) {
     const ResidentFn fn = kernel_of(s);
-    if (!fn.kernel || R < 1 || R > INT32_MAX || 64 * s.waves > fn.max_threads) return hipErrorInvalidValue;
+    // a launch takes fewer than 2^32 threads along x
+    if (!fn.kernel || R < 1 || R * 64 * s.waves > UINT32_MAX || 64 * s.waves > fn.max_threads)
+        return hipErrorInvalidValue;
     const size_t lds = fn.lds(s);
     if (lds > kLdsBytes) return hipErrorInvalidValue;
     if (lds > 64 * 1024) {

@@ -4,7 +4,8 @@ calls itself (so that the library's go there) records the grids that the
 launchers ask for; nothing runs, and no pointer is followed.
 
 * copies of states: 64 GiB and more go in pieces that cover every byte once;
-* adjoint passes: 65535 chains of 32768 nodes."""
+* adjoint passes: 65535 chains of 32768 nodes;
+* graph terms: 2^24 + 8 graphs of two nodes."""
 
 import os
 import shutil
@@ -126,3 +127,10 @@ def test_adjoint_passes_of_the_largest_batches(recorder):
         assert_launchable(grids[0])
         # whole groups of eight realisations, every band of each
         assert grids[0][0] * grids[0][1] == (R + 7) // 8 * 8 * rest["bands"]
+
+
+def test_graph_terms_of_many_small_graphs(recorder):
+    for n, R in ((2, 2 ** 24 + 8), (300, 2 ** 23), (2, 64)):
+        grids, rest = recorder("graph", n, R)
+        assert rest["status"] == 0 and len(grids) == 1
+        assert_launchable(grids[0])
