@@ -1433,6 +1433,23 @@ bool kernel_copies(int32_t on_device, const void* theirs, const void* mine, int6
     return at.type == hipMemoryTypeDevice && am.type == hipMemoryTypeDevice && at.device == am.device;
 }
 
+// A device buffer of the caller's that ends before the state does: the kernel
+// would run past it, where the runtime's copy refuses.
+ctqw_status check_extent(ctqw_plan* p, int32_t on_device, const void* theirs, int64_t bytes) {
+    if (!on_device) return CTQW_OK;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void*>(theirs)) != hipSuccess) {
+        (void)hipGetLastError();   // not an allocation of its own: the copy decides
+        return CTQW_OK;
+    }
+    const int64_t left = (int64_t)size - (static_cast<const char*>(theirs) - static_cast<const char*>(base));
+    if (left < bytes)
+        return fail(p, CTQW_ERR_DEVICE, "the device buffer ends after %lld of the state's %lld bytes", (long long)left,
+                    (long long)bytes);
+    return CTQW_OK;
+}
+
 ctqw_status read_status(ctqw_plan* p, int32_t* st) {
     HIP_TRY(p, hipMemcpyAsync(st, p->ws + p->lay.status.off, 16, hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
@@ -2269,6 +2286,7 @@ ctqw_status ctqw_set_state(ctqw_plan* p, const void* psi, int32_t on_device) {
     ctqw_status st = ensure_ready(p);
     if (st != CTQW_OK) return st;
     const int64_t bytes = p->state_off.back() * (p->prob.dtype == CTQW_C128 ? 16 : 8);
+    if ((st = check_extent(p, on_device, psi, bytes)) != CTQW_OK) return st;
     if (kernel_copies(on_device, psi, p->psi[0], bytes)) HIP_TRY(p, launch_copy(p->psi[0], psi, bytes, p->stream));
     else
         HIP_TRY(p, hipMemcpyAsync(p->psi[0], psi, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
@@ -2289,6 +2307,8 @@ ctqw_status ctqw_get_state(ctqw_plan* p, void* psi, int32_t on_device) {
     if (!p || !psi) return fail(p, CTQW_ERR_INVALID_ARG, "NULL argument");
     ctqw_status st = ensure_ready(p);
     if (st != CTQW_OK) return st;
+    const int64_t bytes = p->state_off.back() * (p->prob.dtype == CTQW_C128 ? 16 : 8);
+    if ((st = check_extent(p, on_device, psi, bytes)) != CTQW_OK) return st;
     if (p->prob.renormalize) {
         RescaleArgs ra{};
         ra.psi = p->psi[p->cur];
@@ -2298,7 +2318,6 @@ ctqw_status ctqw_get_state(ctqw_plan* p, void* psi, int32_t on_device) {
         ra.dtype = p->prob.dtype == CTQW_C128 ? 1 : 0;
         HIP_TRY(p, launch_rescale(ra, p->stream));
     }
-    const int64_t bytes = p->state_off.back() * (p->prob.dtype == CTQW_C128 ? 16 : 8);
     if (kernel_copies(on_device, psi, p->psi[p->cur], bytes))
         HIP_TRY(p, launch_copy(psi, p->psi[p->cur], bytes, p->stream));
     else
