@@ -54,11 +54,11 @@ constexpr int kAutoRowSegments = 128;
 // Three particles: a block (8 waves) takes a compute unit, so batches of
 // fewer tiles leave some idle; their x1 planes are split.
 constexpr int64_t kComputeUnits = 256;
-// The per-step norm partials of kPartSlots steps are held and reduced
-// together; above kSlottedParts partials the reduction is a small part of a step
-// and every step has its own.  One realisation of N = 1024 (657 partials, 23 us
-// per step kernel): 29.0 -> 28.1 us per step; distinguishable N = 129, 24
-// realisations, gradient: 10.10 -> 10.04 ms.
+// The norm partials of up to kPartSlots steps are held and reduced together, as
+// many as kSlottedParts partials hold: of more than half as many the reduction is a
+// small part of a step, and every step has its own.  One realisation of N = 1024
+// (657 partials, 23 us per step kernel): 29.0 -> 28.1 us per step; distinguishable
+// N = 129, 24 realisations, gradient: 10.10 -> 10.04 ms.
 constexpr int kPartSlots = 8;
 constexpr int64_t kSlottedParts = 65536;
 thread_local std::string g_last_error;
@@ -122,6 +122,7 @@ struct ctqw_plan {
     int levels = 0;                  // Taylor terms per step (the batch's order)
     int chunk = 0;                   // terms per pass of a chunked step (0: fused)
     int cols = 1;                    // columns per lane of its steps
+    int room = 0;                    // Roominess of the layout
     ctqw_launch launch{};
     Layout lay;
     bool tables_dirty = true;
@@ -424,7 +425,10 @@ bool make_bands(const ctqw_problem& pr, int r, int N, int h, int W, int align, b
     return true;
 }
 
-ctqw_status build_tables(ctqw_plan* p) {
+// How much workspace a layout may take for speed alone.
+enum Roominess { kRoomy = 0, kOneSlot = 1, kFewSegments = 2 };
+
+ctqw_status build_tables_at(ctqw_plan* p, int room) {
     const ctqw_problem& pr = p->prob;
     int P = p->launch.cols_per_lane;
     int maxn = 0;
@@ -487,7 +491,7 @@ ctqw_status build_tables(ctqw_plan* p) {
                 const int64_t planes = (N + s - 1) / s + (s > 1 || periodic ? 2 * k3 : 0) + k3;
                 return (tiles * s + kComputeUnits - 1) / kComputeUnits * planes;
             };
-            if (tiles < 2 * kComputeUnits)
+            if (tiles < 2 * kComputeUnits && room < kFewSegments)
                 for (int s = 2; s <= N / (2 * k3); ++s)
                     if (cost(s) < cost(segs)) segs = s;
         }
@@ -547,8 +551,9 @@ ctqw_status build_tables(ctqw_plan* p) {
         // rows into segments, each swept from `halo` rows before its first
         // output row to `halo` rows after its last (the rows the pipeline
         // needs to bring its deepest term up to date).
+        const int auto_cap = room < kFewSegments ? kAutoRowSegments : kMaxRowSegments;
         const int seg_cap = p->launch.row_segments == 0
-                                ? ((int64_t)items.size() < kSplitTarget ? kAutoRowSegments : 1)
+                                ? ((int64_t)items.size() < kSplitTarget ? auto_cap : 1)
                                 : p->launch.row_segments;
         if (!chunk && pr.m == 2 && seg_cap > 1) {
             const bool periodic = pr.boundary == CTQW_PERIODIC;
@@ -720,10 +725,14 @@ ctqw_status build_tables(ctqw_plan* p) {
     align_region(L, L.Jf, p->param_total * 4);
     align_region(L, L.Ef, p->param_total * 4);
     align_region(L, L.scale, R * 8);
-    p->part_slots = n_parts <= kSlottedParts ? kPartSlots : 1;
+    // room for kPartSlots steps up to kSlottedParts partials, never less than for
+    // one step: a region that grows with the partials, so that a shape of fewer
+    // bands fits wherever one of more did
+    const int64_t held_parts = room == kRoomy ? std::max(n_parts, std::min(n_parts * kPartSlots, kSlottedParts)) : n_parts;
+    p->part_slots = (int)std::min<int64_t>(kPartSlots, held_parts / std::max<int64_t>(1, n_parts));
     p->part_slot = 0;
-    align_region(L, L.norm_part, n_parts * 8 * p->part_slots);
-    align_region(L, L.tail_part, n_parts * 8 * p->part_slots);
+    align_region(L, L.norm_part, held_parts * 8);
+    align_region(L, L.tail_part, held_parts * 8);
     align_region(L, L.norm2, R * 8);
     align_region(L, L.tail2, R * 8);
     align_region(L, L.status, 16);
@@ -766,6 +775,22 @@ ctqw_status build_tables(ctqw_plan* p) {
     p->drop_graphs();
     ++p->table_version;
     return CTQW_OK;
+}
+
+// The tables and the workspace layout of the current launch shape.  A plan
+// that is bound keeps its workspace: where the layout would not fit, the norm
+// partials of one step are held instead of several's, then rows and planes are
+// split less.  (The order of the shapes by size is not fixed: two columns per
+// lane halve the bands and can end with more segments of them.)
+ctqw_status build_tables(ctqw_plan* p) {
+    ctqw_status st = CTQW_OK;
+    for (int room : {kRoomy, kOneSlot, kFewSegments}) {
+        st = build_tables_at(p, room);
+        p->room = room;
+        if (st != CTQW_OK || !p->bound || p->lay.total <= p->ws_bytes) return st;
+    }
+    p->room = kRoomy;
+    return build_tables_at(p, kRoomy);   // too small for any: refused when used
 }
 
 ctqw_status upload_tables(ctqw_plan* p) {
@@ -2231,7 +2256,9 @@ ctqw_status ctqw_bind(ctqw_plan* p, void* psi_a, void* psi_b, int64_t state_byte
     p->bound = true;
     p->drop_graphs();
     p->tables_dirty = true;
-    ctqw_status st = upload_tables(p);
+    // (a layout made to fit the last workspace may have room in this one)
+    ctqw_status st = p->room == kRoomy ? CTQW_OK : build_tables(p);
+    if (st == CTQW_OK) st = upload_tables(p);
     if (st != CTQW_OK) {
         p->bound = false;
         return st;
