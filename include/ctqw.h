@@ -115,9 +115,8 @@ typedef struct {
 /* Launch shape of the propagation kernels.  Defaults are chosen by the
  * library; ctqw_autotune() measures and stores the best one.  Two particles
  * on small lattices (states that fit one compute unit, at most 128 nodes)
- * with static noise run whole segments of steps on chip, one block per
- * realisation and one launch per segment, whatever the shape, unless
- * `chunked` asks for passes.                                              */
+ * with static noise run up to 256 steps per launch on chip, one block per
+ * realisation, whatever the shape, unless `chunked` asks for passes.     */
 typedef struct {
     int32_t cols_per_lane;   /* 1 or 2 lattice columns per SIMD lane */
     int32_t waves_per_block; /* 1, 2 or 4 */

@@ -5,7 +5,8 @@ launchers ask for; nothing runs, and no pointer is followed.
 
 * copies of states: 64 GiB and more go in pieces that cover every byte once;
 * adjoint passes: 65535 chains of 32768 nodes;
-* graph terms: 2^24 + 8 graphs of two nodes."""
+* graph terms: 2^24 + 8 graphs of two nodes;
+* steps held on chip: a long run in launches of bounded length."""
 
 import os
 import shutil
@@ -20,11 +21,14 @@ PROGRAM = r"""
 #include "ctqw_internal.hpp"
 #include "adjoint_pipe.hpp"
 #include "graph.hpp"
+#include "resident.hpp"
+#include "ctqw.h"
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 
-namespace { dim3 g_grid, g_block; size_t g_lds; hipStream_t g_stream; bool g_copy; }
+namespace { dim3 g_grid, g_block; size_t g_lds; hipStream_t g_stream; bool g_copy; const void* g_only; }
 
 extern "C" {
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
@@ -35,7 +39,14 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     *grid = g_grid; *block = g_block; *lds = g_lds; *stream = g_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+    if (g_only) {   // on-chip steps: steps, and where they start and end
+        const auto* a = (const ctqw::ResidentArgs*)args[0];
+        if (fn == g_only)
+            std::printf("launch %lld %llu %llu %lld\n", (long long)a->steps, (unsigned long long)a->psi_in,
+                        (unsigned long long)a->psi_out, (long long)a->out_stride);
+        return hipSuccess;
+    }
     std::printf("launch %u %u %u %u", grid.x, grid.y, grid.z, block.x);
     if (g_copy)   // source, destination, 16-byte elements, words after them
         std::printf(" %llu %llu %lld %d", (unsigned long long)*(void**)args[0], (unsigned long long)*(void**)args[1],
@@ -45,6 +56,13 @@ hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size
 }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void* dst, const void*, size_t n, hipMemcpyKind kind, hipStream_t) {
+    if (kind == hipMemcpyDeviceToHost) std::memset(dst, 0, n);
+    return hipSuccess;
+}
 }
 
 int main(int argc, char** argv) {
@@ -71,6 +89,40 @@ int main(int argc, char** argv) {
         a.R = std::atoi(argv[3]);
         a.width = 1;
         e = launch_graph_term(a, 1, nullptr);
+    }
+    else if (!std::strcmp(argv[1], "steps")) {
+        const int N = 20, R = 3;
+        ResidentShape s;
+        if (!resident_shape(kResTri, 1, 0, N, 6, R, &s)) return 1;
+        g_only = (const void*)resident_tri(s).kernel;
+        ctqw_problem pr{};
+        pr.m = 2;
+        pr.statistics = CTQW_BOSON;
+        pr.dtype = CTQW_C128;
+        pr.R = R;
+        pr.n_sites = N;
+        pr.dt = 0.05;
+        pr.taylor_order = 6;
+        ctqw_plan* p = nullptr;
+        std::vector<double> J(R * (N - 1), 1.0), eps(R * N, 0.0), U(R, 0.0), w(N, 1.0), g(2 * N);
+        double loss;
+        char* const base = (char*)(1ull << 40);
+        int32_t sites[2] = {1, 2};
+        int64_t state, work, grad;
+        const int64_t n = std::atoll(argv[2]), every = std::atoll(argv[3]);
+        int st = ctqw_plan_create(&pr, &p);
+        if (!st) st = ctqw_set_params(p, J.data(), eps.data(), U.data());
+        if (!st) st = ctqw_sizes(p, &state, &work);
+        if (!st) st = ctqw_bind(p, base, base + (1 << 28), state, base + (1 << 29), work, nullptr);
+        if (!st) st = ctqw_init_product_state(p, sites, 0);
+        if (!st && !every) st = ctqw_propagate(p, n, 0, 0, nullptr);
+        if (!st && every) st = ctqw_gradient_workspace(p, n, every, &grad);
+        if (!st && every)
+            st = ctqw_gradient(p, n, every, CTQW_LOSS_PRODUCT, w.data(), base + (1ull << 32), grad, &loss, g.data(),
+                               g.data() + N);
+        e = (hipError_t)st;
+        std::printf("state %lld\n", (long long)state);
+        ctqw_plan_destroy(p);
     }
     std::printf("status %d\n", (int)e);
     return 0;
@@ -134,3 +186,27 @@ def test_graph_terms_of_many_small_graphs(recorder):
         grids, rest = recorder("graph", n, R)
         assert rest["status"] == 0 and len(grids) == 1
         assert_launchable(grids[0])
+
+
+@pytest.mark.parametrize("n", [1, 256, 257, 100000])
+def test_long_runs_on_chip_are_cut(recorder, n):
+    """propagate: every launch at most 256 steps, in place."""
+    grids, rest = recorder("steps", n, 0)
+    assert rest["status"] == 0
+    assert sum(g[0] for g in grids) == n and all(1 <= g[0] <= 256 for g in grids)
+    assert all(g[1] == g[2] and g[3] == 0 for g in grids)
+
+
+@pytest.mark.parametrize("n,every", [(700, 700), (40, 40), (1024, 512)])
+def test_recomputed_segments_on_chip_are_cut(recorder, n, every):
+    """gradient: a segment's states are stored one after the other, a launch
+    starting from the state that the one before it stored last."""
+    grids, rest = recorder("steps", n, every)
+    assert rest["status"] == 0 and all(1 <= g[0] <= 256 for g in grids)
+    stored = [g for g in grids if g[3]]
+    assert sum(g[0] for g in grids if not g[3]) == n and sum(g[0] for g in stored) == n // every * (every - 1)
+    at = 0
+    for a, b in zip(stored, stored[1:]):
+        at += a[0]
+        if at % (every - 1):   # inside a segment
+            assert b[2] == a[2] + a[0] * a[3] and b[1] == b[2] - b[3]
