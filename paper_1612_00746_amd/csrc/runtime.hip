@@ -562,15 +562,24 @@ ctqw_status build_tables_at(ctqw_plan* p, int room) {
                                 : p->launch.row_segments;
         if (!chunk && pr.m == 2 && seg_cap > 1) {
             const bool periodic = pr.boundary == CTQW_PERIODIC;
-            // Full-grid complex128 waves have a SIMD to themselves, and a few items
-            // past one per SIMD take a second round: round down (N = 704, order 7:
-            // R = 4 74 us per step rounding up, 45 down; R = 16 158 / 96; N = 256,
-            // order 9, R = 40 99 / 68).  A triangle's short bands split less, so
-            // its items stay below the target (N = 256, R = 60 106 up, 135 down),
-            // and complex64 has two waves per SIMD.
+            // Full grids.  A kernel that holds one wave per SIMD (complex64 with 12
+            // terms, complex128 from 8) takes a second round for a few items past
+            // one per SIMD: round down (us per step rounding up / down: complex64
+            // N = 2000, R = 1, 12 terms 145 / 96; complex128 N = 704, R = 16, 7
+            // terms 158 / 96; N = 256, R = 40, 9 terms 99 / 68).  complex128 at 6
+            // and 7 terms, two waves whose FP64 fills a SIMD, likewise.  Where two
+            // waves do share a SIMD well, a few items past the target still
+            // double some SIMDs' work (complex64 N = 1104, R = 1, 7 terms: 1034
+            // items 9 % slower than 1012) but a half more of them fill it (N =
+            // 839, R = 33, 3 terms: 1485 items 11 % faster than 990).  A triangle's
+            // short bands split less, so its items stay below the target (N = 256,
+            // R = 60: 106 us up, 135 down).
             const int64_t n = (int64_t)items.size();
-            const bool down = dtype == 1 && pr.statistics == CTQW_DISTINGUISHABLE && 2 * n <= kSplitTarget;
-            const int64_t fit = down ? kSplitTarget / n : (kSplitTarget + n - 1) / n;
+            const int64_t lo = kSplitTarget / n, hi = (kSplitTarget + n - 1) / n;
+            const bool down = pr.statistics == CTQW_DISTINGUISHABLE && 2 * n <= kSplitTarget &&
+                              (levels >= (dtype == 1 ? 6 : 12) ||
+                               (10 * lo * n >= 9 * kSplitTarget && 5 * hi * n <= 6 * kSplitTarget));
+            const int64_t fit = down ? lo : hi;
             const int64_t want = p->launch.row_segments == 0 ? fit : seg_cap;
             const int S = (int)std::min<int64_t>(seg_cap, want);
             std::vector<ItemDev> split;
