@@ -116,7 +116,10 @@ typedef struct {
  * library; ctqw_autotune() measures and stores the best one.  Two particles
  * on small lattices (states that fit one compute unit, at most 128 nodes)
  * with static noise run up to 256 steps per launch on chip, one block per
- * realisation, whatever the shape, unless `chunked` asks for passes.     */
+ * realisation, whatever the shape, unless `chunked` asks for passes or an
+ * estimate favours band sweeps: mostly realisations much smaller than the
+ * largest, or a call of few steps on states beyond the caches.  The two agree
+ * to rounding, complex64 full grids bit for bit.                          */
 typedef struct {
     int32_t cols_per_lane;   /* 1 or 2 lattice columns per SIMD lane */
     int32_t waves_per_block; /* 1, 2 or 4 */

@@ -3,6 +3,8 @@
 
 #include "ctqw_internal.hpp"
 
+#include <vector>
+
 namespace ctqw {
 
 // Deepest series of the resident kernel (its coefficients are arguments).
@@ -45,6 +47,19 @@ struct ResidentShape {
 // Shape for the batch's largest lattice, or false if a realisation's state
 // does not fit one compute unit (or the order is too deep).
 bool resident_shape(int layout, int dtype, int kahan, int max_N, int max_order, int64_t R, ResidentShape* out);
+// One step of the batch as band sweeps.
+struct BandLaunch {
+    int order = 0;          // terms
+    int64_t items = 0;
+    int64_t rows = 0;       // swept, over all items, with the pipeline's depth
+    int longest = 0;        // of one item
+};
+// Estimated us of a step in these launches (passes > 1: the one launch is each
+// pass's share).
+double band_step_us(int layout, int dtype, int cols, int passes, const std::vector<BandLaunch>& launches, int64_t bytes);
+// Whether `steps` steps (of `bytes` of state, each band_us as bands) take less
+// time on chip.
+bool resident_pays(const ResidentShape& s, int64_t R, int order, int64_t bytes, int64_t steps, double band_us);
 // A compiled shape: its kernel, the block it was compiled for, its LDS bytes.
 struct ResidentFn {
     void (*kernel)(ResidentArgs) = nullptr;

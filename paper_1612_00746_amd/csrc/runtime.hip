@@ -128,6 +128,7 @@ struct ctqw_plan {
     int chunk = 0;                   // terms per pass of a chunked step (0: fused)
     int cols = 1;                    // columns per lane of its steps
     int room = 0;                    // Roominess of the layout
+    double band_us = 0;              // estimate of a step as band sweeps (two particles)
     ctqw_launch launch{};
     Layout lay;
     bool tables_dirty = true;
@@ -430,6 +431,11 @@ bool make_bands(const ctqw_problem& pr, int r, int N, int h, int W, int align, b
     return true;
 }
 
+int on_chip_layout(const ctqw_problem& pr) {
+    if (pr.statistics != CTQW_DISTINGUISHABLE) return kResTri;
+    return pr.boundary == CTQW_PERIODIC ? kResRing : kResFull;
+}
+
 // How much workspace a layout may take for speed alone.
 enum Roominess { kRoomy = 0, kOneSlot = 1, kFewSegments = 2 };
 
@@ -723,6 +729,25 @@ ctqw_status build_tables_at(ctqw_plan* p, int room) {
     p->levels = levels;
     p->chunk = chunk;
     p->cols = chunk ? 1 : P;
+    if (pr.m == 2) {
+        std::vector<BandLaunch> launches;
+        auto add = [&](int order, int32_t k0, int32_t k1) {
+            BandLaunch l;
+            l.order = order;
+            l.items = k1 - k0;
+            for (int32_t k = k0; k < k1; ++k) {
+                const int rows = p->items[p->item_order[k]].nrows + order;
+                l.rows += rows;
+                l.longest = std::max(l.longest, rows);
+            }
+            launches.push_back(l);
+        };
+        if (chunk) add(levels, 0, (int32_t)p->items.size());
+        else
+            for (const auto& run : p->order_runs) add(run[0], run[1], run[2]);
+        p->band_us = band_step_us(on_chip_layout(pr), dtype, p->cols, chunk ? (levels + chunk - 1) / chunk : 1, launches,
+                                  p->state_off.back() * amp_bytes);
+    }
 
     // workspace layout
     Layout L;
@@ -1195,15 +1220,15 @@ ctqw_status enqueue_telegraph(ctqw_plan* p) {
     return CTQW_OK;
 }
 
-// Whether the plan's steps run on chip (resident.hpp), and in which shape.
-bool resident_ok(const ctqw_plan* p, ResidentShape* s) {
+// Whether `steps` steps of one call run on chip (resident.hpp), and in which
+// shape.
+bool resident_ok(const ctqw_plan* p, int64_t steps, ResidentShape* s) {
     const ctqw_problem& pr = p->prob;
     // passes asked for, or a Hamiltonian that changes between steps
     if (pr.m != 2 || p->launch.chunked || p->tele_amp > 0.0) return false;
-    const int layout = pr.statistics != CTQW_DISTINGUISHABLE ? kResTri
-                                                              : (pr.boundary == CTQW_PERIODIC ? kResRing : kResFull);
-    return resident_shape(layout, pr.dtype == CTQW_C128 ? 1 : 0, pr.accumulation == CTQW_ACC_KAHAN ? 1 : 0, p->max_N,
-                          p->levels, pr.R, s);
+    return resident_shape(on_chip_layout(pr), pr.dtype == CTQW_C128 ? 1 : 0,
+                          pr.accumulation == CTQW_ACC_KAHAN ? 1 : 0, p->max_N, p->levels, pr.R, s) &&
+           resident_pays(*s, pr.R, p->levels, p->state_off.back() * (pr.dtype == CTQW_C128 ? 16 : 8), steps, p->band_us);
 }
 
 // `steps` steps from `in`, norm checks included.  stride > 0:
@@ -1257,8 +1282,6 @@ ctqw_status enqueue_resident_steps(ctqw_plan* p, const ResidentShape& s, int64_t
 ctqw_status enqueue_step(ctqw_plan* p) {
     if (p->prob.m == 3) return enqueue_step3(p);
     ctqw_status st;
-    ResidentShape rs;
-    if (resident_ok(p, &rs)) return enqueue_resident_steps(p, rs, 1);
     if ((st = enqueue_telegraph(p)) != CTQW_OK) return st;
     if (p->timing && (st = record_event(p, 0)) != CTQW_OK) return st;
     if ((st = enqueue_step_kernels(p, p->psi[p->cur], p->psi[1 - p->cur])) != CTQW_OK) return st;
@@ -1326,7 +1349,7 @@ ctqw_status enqueue_stored_steps(ctqw_plan* p, int64_t len, uint8_t* seg, int64_
 ctqw_status enqueue_steps(ctqw_plan* p, int64_t count) {
     if (count <= 0) return CTQW_OK;
     ResidentShape rs;
-    if (resident_ok(p, &rs)) return enqueue_resident_steps(p, rs, count);
+    if (resident_ok(p, count, &rs)) return enqueue_resident_steps(p, rs, count);
     if (!p->launch.use_graph || count < 2) return enqueue_step_loop(p, count);
     constexpr int64_t kMaxCaptured = 256;
     if (!p->cap_stream) HIP_TRY(p, hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking));
@@ -2748,7 +2771,7 @@ ctqw_status ctqw_forward_ckpt(ctqw_plan* p, int64_t n_steps, int64_t ckpt_every,
     // forward, keeping the state at steps 0, C, 2C, ...; every realisation
     // runs the batch's largest order, the polynomial the adjoint inverts
     ResidentShape rs;
-    const bool resident = resident_ok(p, &rs);
+    const bool resident = resident_ok(p, std::min(C, n_steps), &rs);   // one path for the whole gradient
     for (int64_t k = 0; k < n_steps;) {
         if (k % C == 0)
             HIP_TRY(p, launch_copy(G + g.ckpt + (k / C) * g.S, p->psi[p->cur], bytes, s));
@@ -2848,7 +2871,7 @@ ctqw_status ctqw_backward(ctqw_plan* p, int32_t kind, const double* site_w, void
     };
 
     ResidentShape rs;
-    const bool resident = resident_ok(p, &rs);
+    const bool resident = resident_ok(p, std::min(C, n_steps), &rs);   // as the forward run
     int lc = 0;   // state(g.lam, lc) holds lambda_{k+1}
     std::vector<const void*> segp(C), vp(n);
     for (int64_t sg = g.n_ckpt - 1; sg >= 0 && n_steps > 0; --sg) {

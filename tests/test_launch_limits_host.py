@@ -6,7 +6,9 @@ launchers ask for; nothing runs, and no pointer is followed.
 * copies of states: 64 GiB and more go in pieces that cover every byte once;
 * adjoint passes: 65535 chains of 32768 nodes;
 * graph terms: 2^24 + 8 graphs of two nodes;
-* steps held on chip: a long run in launches of bounded length."""
+* steps held on chip: a long run in launches of bounded length;
+* which calls run on chip: not those of batches whose realisations are mostly much
+  smaller than the largest, nor short calls on states beyond the caches."""
 
 import os
 import shutil
@@ -59,6 +61,7 @@ hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipS
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) { *a = {}; a->maxThreadsPerBlock = 256; return hipSuccess; }
 hipError_t hipMemcpyAsync(void* dst, const void*, size_t n, hipMemcpyKind kind, hipStream_t) {
     if (kind == hipMemcpyDeviceToHost) std::memset(dst, 0, n);
     return hipSuccess;
@@ -122,6 +125,39 @@ int main(int argc, char** argv) {
                                g.data() + N);
         e = (hipError_t)st;
         std::printf("state %lld\n", (long long)state);
+        ctqw_plan_destroy(p);
+    } else if (!std::strcmp(argv[1], "route")) {
+        // statistics, boundary, dtype, largest lattice, how many, the others' size, how many, order, steps
+        const int N = std::atoi(argv[5]), n1 = std::atoi(argv[6]), small = std::atoi(argv[7]), n2 = std::atoi(argv[8]);
+        ctqw_problem pr{};
+        pr.m = 2;
+        pr.statistics = std::atoi(argv[2]);
+        pr.boundary = std::atoi(argv[3]);
+        pr.dtype = std::atoi(argv[4]);
+        pr.R = n1 + n2;
+        std::vector<int32_t> Ns(n1, N);
+        Ns.resize(pr.R, small);
+        pr.n_sites_per_real = Ns.data();
+        pr.dt = 0.05;
+        pr.taylor_order = std::atoi(argv[9]);
+        int64_t sites = 0, state, work;
+        for (int x : Ns) sites += x;
+        std::vector<double> J(sites, 1.0), eps(sites, 0.0), U(pr.R, 0.0);
+        ctqw_plan* p = nullptr;
+        char* const base = (char*)(1ull << 40);
+        int32_t at[2] = {1, 2};
+        const int layout = pr.statistics ? kResTri : (pr.boundary ? kResRing : kResFull);
+        ResidentShape s;
+        if (!resident_shape(layout, pr.dtype, pr.dtype ? 0 : 1, N, pr.taylor_order, pr.R, &s)) return 1;
+        g_only = (const void*)(layout == kResTri ? resident_tri(s) : layout == kResRing ? resident_ring(s)
+                                                                                         : resident_full(s)).kernel;
+        int st = ctqw_plan_create(&pr, &p);
+        if (!st) st = ctqw_set_params(p, J.data(), eps.data(), U.data());
+        if (!st) st = ctqw_sizes(p, &state, &work);
+        if (!st) st = ctqw_bind(p, base, base + (1ull << 36), state, base + (1ull << 37), work, nullptr);
+        if (!st) st = ctqw_init_product_state(p, at, 0);
+        if (!st) st = ctqw_propagate(p, std::atoll(argv[10]), 0, 0, nullptr);
+        e = (hipError_t)st;
         ctqw_plan_destroy(p);
     }
     std::printf("status %d\n", (int)e);
@@ -210,3 +246,38 @@ def test_recomputed_segments_on_chip_are_cut(recorder, n, every):
         at += a[0]
         if at % (every - 1):   # inside a segment
             assert b[2] == a[2] + a[0] * a[3] and b[1] == b[2] - b[3]
+
+
+GRID, BOSON = 0, 1
+OPEN, RING = 0, 1
+C64, C128 = 0, 1
+
+
+@pytest.mark.parametrize("batch,steps,on_chip", [
+    # one large lattice among small ones
+    ((GRID, OPEN, C64, 128, 1, 16, 4095, 7), 20, False),
+    ((GRID, OPEN, C128, 96, 1, 16, 4095, 10), 20, False),
+    ((BOSON, OPEN, C64, 128, 1, 16, 4095, 7), 20, False),
+    ((GRID, OPEN, C128, 96, 1, 32, 1000, 10), 20, False),
+    ((GRID, OPEN, C64, 128, 1, 16, 255, 7), 20, True),
+    ((BOSON, OPEN, C128, 128, 500, 60, 500, 10), 20, True),
+    # large states: short calls, and lattices that leave waves idle
+    ((GRID, OPEN, C64, 96, 8000, 0, 0, 7), 1, False),
+    ((GRID, OPEN, C64, 80, 8000, 0, 0, 7), 16, False),
+    ((GRID, OPEN, C64, 64, 16000, 0, 0, 7), 1, False),
+    ((GRID, OPEN, C64, 64, 16000, 0, 0, 7), 16, True),
+    ((GRID, RING, C64, 48, 16000, 0, 0, 7), 16, False),
+    ((BOSON, OPEN, C64, 128, 16000, 0, 0, 7), 1, False),
+    ((BOSON, OPEN, C64, 128, 16000, 0, 0, 7), 16, True),
+    # few realisations of the widest shapes
+    ((GRID, OPEN, C64, 128, 1, 0, 0, 7), 4, True),
+    ((GRID, OPEN, C64, 128, 1, 0, 0, 7), 1, False),
+    ((GRID, RING, C128, 96, 1, 0, 0, 10), 30, False),
+    # what the on-chip steps are for
+    ((BOSON, OPEN, C128, 128, 1000, 0, 0, 12), 1, True),
+    ((GRID, OPEN, C128, 16, 8, 0, 0, 9), 1, True),
+    ((GRID, OPEN, C64, 64, 1000, 0, 0, 7), 4, True),
+])
+def test_calls_go_on_chip_where_that_is_faster(recorder, batch, steps, on_chip):
+    grids, rest = recorder("route", *batch, steps)
+    assert rest["status"] == 0 and sum(g[0] for g in grids) == (steps if on_chip else 0)
