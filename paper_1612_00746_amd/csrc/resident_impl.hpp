@@ -285,10 +285,14 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
     const int dlast = max(0, K - 1 - k0);
     const T* const bj0 = TRI ? tabJ + (P == 1 ? lane + k0 : (k0 & 1) * bond_plane<P>() + lane + (k0 >> 1)) : nullptr;
     const T* const bj1 = TRI && P == 2 ? tabJ + ((k0 + 1) & 1) * bond_plane<P>() + lane + ((k0 + 1) >> 1) : nullptr;
+    // The last level's squares, before the 1/n! that scales them: a triangle's in
+    // FP64, as deep series leave FP32's range; a grid's per lane in the state's
+    // precision (either as the bands do; FP64 costs the grids 5 %).
+    using Tail = std::conditional_t<TRI, double, T>;
     // One level, in place: t <- (dt H) t; the sum takes the new vector with
     // the factor (-i)^j / j!: ODD levels swap the parts.  Rows 1 .. S - 1
     // first, then row 0: the neighbouring waves' rows are needed last.
-    auto level = [&](auto odd, T c, bool last, double& tail) {
+    auto level = [&](auto odd, T c, bool last, Tail& tail) {
         constexpr bool ODD = decltype(odd)::value;
         const C* base = pub + buf * slots * 64 * P;
         T lr[P], li[P], hr[P], hi[P];
@@ -471,13 +475,11 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 const int k = kb + s;
-                // in FP64: the squares of a deep last term leave FP32's range
-                // before the 1/n! that brings them back is applied
-                const double w = TRI && k != 0 && 2 * k != N ? 2.0 : 1.0;
+                const Tail w = TRI && k != 0 && 2 * k != N ? Tail(2) : Tail(1);
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
-                    const double x = tr[s][p], y = ti[s][p];
-                    if (k < K) tail = __builtin_fma(w, __builtin_fma(x, x, y * y), tail);
+                    const Tail x = tr[s][p], y = ti[s][p];
+                    if (k < K) tail = fma_t(w, fma_t(x, x, y * y), tail);
                 }
             }
         }
@@ -512,7 +514,7 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
                     ai[s][p] = ti[s][p];
                 }
             }
-        double tail = 0.0;
+        Tail tail = Tail(0);
         T sgn = T(1);
         T c1 = static_cast<T>(a.coef[1]), c2 = static_cast<T>(a.coef[2]);
         for (int j = 1; j <= n; j += 2) {
@@ -577,7 +579,7 @@ __global__ void __launch_bounds__(MAXT) resident_kernel(ResidentArgs a) {
             }
         }
         nrm = wave_sum_last(nrm);
-        const double tl = wave_sum_last(tail);
+        const double tl = wave_sum_last((double)tail);
         double* pp = part + ppar * 2 * W;
         if (lane == 63) {
             pp[2 * wv] = nrm;
