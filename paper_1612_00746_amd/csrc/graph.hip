@@ -51,28 +51,29 @@ template <typename T> struct RealsPerThread;
 template <> struct RealsPerThread<float> { static constexpr int value = 4; };
 template <> struct RealsPerThread<double> { static constexpr int value = 1; };
 
-// Sum of one double per thread of a block of 256, the same on every run; the
-// result is thread 0's.
-__device__ inline double block_sum(double v, double* part) {
-    const int t = (int)threadIdx.x;
-    part[t] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) part[t] += part[t + w];
-        __syncthreads();
-    }
-    const double sum = part[0];
-    __syncthreads();
-    return sum;
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_part(double v) {
+    return __builtin_amdgcn_update_dpp(0.0, v, CTRL, ROWS, 0xF, true);
+}
+// Sum over the wave, valid in lane 63.
+__device__ __forceinline__ double wave_sum_last(double v) {
+    v += dpp_part<0x111, 0xF>(v);   // row_shr:1
+    v += dpp_part<0x112, 0xF>(v);   // row_shr:2
+    v += dpp_part<0x114, 0xF>(v);   // row_shr:4
+    v += dpp_part<0x118, 0xF>(v);   // row_shr:8
+    v += dpp_part<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    v += dpp_part<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
 }
 
-// NORM: the last term of a step; the block's part of the squared norms goes to a.parts.
-template <typename T, bool NORM>
+// Q: realisations per thread.  NORM: the last term of a step; the block's part
+// of the squared norms goes to a.parts (summed over each wave, then over the
+// four: one barrier, where a tree in LDS takes ten per realisation).
+template <typename T, int Q, bool NORM>
 __global__ __launch_bounds__(256) void graph_term_kernel(GraphTermArgs a) {
     using C = typename Cplx<T>::type;
-    constexpr int Q = RealsPerThread<T>::value;
     constexpr int S = 4;   // slots whose loads are in flight together
-    __shared__ double part[NORM ? 256 : 1];
+    __shared__ double part[NORM ? 4 : 1][Q];
     const int64_t n = a.n;
     const T* hop = static_cast<const T*>(a.hop);
     const T* onsite = static_cast<const T*>(a.onsite);
@@ -106,27 +107,45 @@ __global__ __launch_bounds__(256) void graph_term_kernel(GraphTermArgs a) {
             hi[q] = e * x[q].y;
         }
         // No branch around the loads: an empty slot reads node i and its sum
-        // is dropped.
+        // is dropped.  One realisation per thread: after a group with empty slots
+        // the next is looked at first (its couplings then wait for the indices)
+        // and passed over if it is empty at all of the wave's nodes.
+        bool gaps = false;
         int32_t k0 = 0;
         auto slots = [&](auto count) {
             constexpr int M = decltype(count)::value;
+            constexpr bool LOOK = Q == 1 && M == S;
             int32_t j[M];
-            bool has[M];
+            bool has[M], any = false, all = true;
             T c[M][Q];
             C xj[M][Q];
+            auto couplings = [&]() {
+#pragma unroll
+                for (int k = 0; k < M; ++k)
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) c[k][q] = hop[(row[q] * a.width + k0 + k) * n + ic];
+            };
+#pragma unroll
+            for (int k = 0; k < M; ++k) j[k] = a.nbr[(int64_t)(k0 + k) * n + ic];
+            if (!LOOK || !gaps) couplings();
 #pragma unroll
             for (int k = 0; k < M; ++k) {
-                j[k] = a.nbr[(int64_t)(k0 + k) * n + ic];
                 has[k] = j[k] >= 0 && j[k] < a.n;
+                any = any || has[k];
+                all = all && has[k];
                 j[k] = has[k] ? j[k] : ic;
+            }
+            if (LOOK && gaps) {
+                if (__builtin_amdgcn_ballot_w64(any) == 0) {
+                    k0 += M;
+                    return;
+                }
+                couplings();
             }
 #pragma unroll
             for (int k = 0; k < M; ++k)
 #pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    c[k][q] = hop[(row[q] * a.width + k0 + k) * n + ic];
-                    xj[k][q] = src[row[q] * n + j[k]];
-                }
+                for (int q = 0; q < Q; ++q) xj[k][q] = src[row[q] * n + j[k]];
 #pragma unroll
             for (int k = 0; k < M; ++k)
 #pragma unroll
@@ -134,6 +153,7 @@ __global__ __launch_bounds__(256) void graph_term_kernel(GraphTermArgs a) {
                     hr[q] = has[k] ? fma_r(c[k][q], xj[k][q].x, hr[q]) : hr[q];
                     hi[q] = has[k] ? fma_r(c[k][q], xj[k][q].y, hi[q]) : hi[q];
                 }
+            if constexpr (LOOK) gaps = __builtin_amdgcn_ballot_w64(!all) != 0;
             k0 += M;
         };
         while (k0 + S <= a.width) slots(std::integral_constant<int, S>{});
@@ -161,26 +181,33 @@ __global__ __launch_bounds__(256) void graph_term_kernel(GraphTermArgs a) {
                 n2 = fma(re, re, im * im);
             }
             if constexpr (NORM) {
-                const double sum = block_sum(n2, part);
-                if (threadIdx.x == 0 && q < nr) a.parts[(r0 + q) * a.node_blocks + bx] = sum;
+                const double sum = wave_sum_last(n2);
+                if ((threadIdx.x & 63) == 63) part[threadIdx.x >> 6][q] = sum;
             }
+        }
+        if constexpr (NORM) {
+            __syncthreads();
+            const int q = (int)threadIdx.x;
+            if (q < nr) a.parts[(r0 + q) * a.node_blocks + bx] = ((part[0][q] + part[1][q]) + part[2][q]) + part[3][q];
+            __syncthreads();
         }
     }
 }
 
 // out[r]: the parts of one realisation, in a fixed order.
 __global__ __launch_bounds__(256) void graph_norm_kernel(const double* parts, int32_t per_real, double* out) {
-    __shared__ double part[256];
+    __shared__ double part[4];
     const double* x = parts + blockIdx.x * (int64_t)per_real;
     double acc = 0.0;
     for (int32_t i = (int32_t)threadIdx.x; i < per_real; i += 256) acc += x[i];
-    const double sum = block_sum(acc, part);
-    if (threadIdx.x == 0) out[blockIdx.x] = sum;
+    acc = wave_sum_last(acc);
+    if ((threadIdx.x & 63) == 63) part[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) out[blockIdx.x] = ((part[0] + part[1]) + part[2]) + part[3];
 }
 
-template <typename T>
+template <typename T, int Q>
 hipError_t launch_term(GraphTermArgs a, hipStream_t s) {
-    constexpr int Q = RealsPerThread<T>::value;
     const int64_t groups = ((int64_t)a.R + Q - 1) / Q;
     a.node_blocks = (int32_t)(((int64_t)a.n + 255) / 256);
     // One XCD per group where the fullest XCD has at most a quarter more than
@@ -192,15 +219,19 @@ hipError_t launch_term(GraphTermArgs a, hipStream_t s) {
     a.by_xcd = rounds * 8 * 4 <= groups * 5 && blocks < int64_t(1) << 24;
     const dim3 grid = a.by_xcd ? dim3((unsigned)blocks)
                                : dim3((unsigned)a.node_blocks, (unsigned)std::min<int64_t>(groups, 65535));
-    if (a.parts) hipLaunchKernelGGL((graph_term_kernel<T, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((graph_term_kernel<T, false>), grid, dim3(256), 0, s, a);
+    if (a.parts) hipLaunchKernelGGL((graph_term_kernel<T, Q, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((graph_term_kernel<T, Q, false>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_graph_term(const GraphTermArgs& a, int dtype, hipStream_t s) {
-    return dtype == 1 ? launch_term<double>(a, s) : launch_term<float>(a, s);
+    if (dtype == 1) return launch_term<double, RealsPerThread<double>::value>(a, s);
+    // fewer realisations than a thread's share would repeat one of them (one
+    // realisation of 5000 nodes, width 12, 3 steps of 8 terms: 228 us in fours, 141)
+    constexpr int Q = RealsPerThread<float>::value;
+    return a.R < Q ? launch_term<float, 1>(a, s) : launch_term<float, Q>(a, s);
 }
 
 hipError_t launch_graph_norms(const double* parts, int32_t n, int32_t R, double* out, hipStream_t s) {
