@@ -495,7 +495,8 @@ ctqw_status ctqw_set_launch(ctqw_plan* plan, const ctqw_launch* launch);
  * band) of one step and the number of waves that one step launches, for
  * the current launch shape (regular: whole blocks of waves_per_block
  * waves; persistent: the device's resident waves, known once bound; with
- * several orders, the largest of the per-order launches).                */
+ * several orders, the largest of the per-order launches).  Calls that run on
+ * chip (see ctqw_launch) launch one block per realisation instead.        */
 ctqw_status ctqw_work_items(const ctqw_plan* plan, int64_t* items, int64_t* waves);
 
 /* Derivatives of an ensemble-averaged diagonal observable.  The paper does
@@ -556,7 +557,9 @@ ctqw_status ctqw_gradient(ctqw_plan* plan, int64_t n_steps, int64_t ckpt_every, 
  * orders) is applied without timing, and new results are appended (one
  * JSON object per line).  If the CTQW_TUNE_TRACE environment variable
  * names a file, one line per candidate (its shape and time, or that it does
- * not fit the bound workspace) is appended to it.  The state buffers are
+ * not fit the bound workspace) is appended to it.  Where runs go on chip
+ * whatever the shape, none is compared: the current one is returned (and
+ * stored), with the time of a step of a run of `steps`.  The state buffers are
  * overwritten: tune before ctqw_init_product_state / ctqw_set_state.
  * best / best_ms may be NULL.                                              */
 ctqw_status ctqw_autotune(ctqw_plan* plan, const char* cache_path, int32_t steps, ctqw_launch* best,

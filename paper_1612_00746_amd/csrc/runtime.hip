@@ -2543,6 +2543,26 @@ ctqw_status time_steps(ctqw_plan* p, int32_t steps, double* ms) {
     return CTQW_OK;
 }
 
+// The same of a run on chip.
+ctqw_status time_on_chip(ctqw_plan* p, const ResidentShape& rs, int32_t steps, double* ms) {
+    const bool was = p->timing;
+    const double t0 = p->timed_ms;
+    const int64_t n0 = p->timed_launches;
+    ctqw_status st;
+    p->timing = false;
+    st = enqueue_resident_steps(p, rs, steps);   // warm-up
+    p->timing = true;
+    p->timed_ms = 0.0;
+    p->timed_launches = 0;
+    if (st == CTQW_OK) st = enqueue_resident_steps(p, rs, steps);
+    if (st == CTQW_OK) st = collect_timing(p);
+    if (st == CTQW_OK) *ms = p->timed_ms / steps;
+    p->timing = was;
+    p->timed_ms = t0;
+    p->timed_launches = n0;
+    return st;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2599,6 +2619,11 @@ ctqw_status ctqw_autotune(ctqw_plan* p, const char* cache_path, int32_t steps, c
             build_tables(p);
             return fail(p, CTQW_ERR_UNSUPPORTED, "no launch shape fits the bound workspace");
         }
+        if (path && *path) cache_append(path, key, best, best_ms);
+    } else if (ResidentShape rs; !cached && resident_ok(p, kResidentSteps, &rs)) {
+        // runs go on chip, whatever the shape: their step is timed, none compared
+        best = orig;
+        if ((st = time_on_chip(p, rs, steps, &best_ms)) != CTQW_OK) return st;
         if (path && *path) cache_append(path, key, best, best_ms);
     } else if (!cached) {
         for (int mode : {0, 1})
