@@ -29,6 +29,7 @@
 // 24 x 24 nodes, 16 realisations, 127 -> 68 us; one walker on 128 x 128, 256
 // realisations, 92 -> 66 (complex64 46 -> 31).
 #include "graph.hpp"
+#include "wave_sum.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -50,21 +51,6 @@ __device__ inline double fma_r(double a, double b, double c) { return __builtin_
 template <typename T> struct RealsPerThread;
 template <> struct RealsPerThread<float> { static constexpr int value = 4; };
 template <> struct RealsPerThread<double> { static constexpr int value = 1; };
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_part(double v) {
-    return __builtin_amdgcn_update_dpp(0.0, v, CTRL, ROWS, 0xF, true);
-}
-// Sum over the wave, valid in lane 63.
-__device__ __forceinline__ double wave_sum_last(double v) {
-    v += dpp_part<0x111, 0xF>(v);   // row_shr:1
-    v += dpp_part<0x112, 0xF>(v);   // row_shr:2
-    v += dpp_part<0x114, 0xF>(v);   // row_shr:4
-    v += dpp_part<0x118, 0xF>(v);   // row_shr:8
-    v += dpp_part<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_part<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
 
 // Q: realisations per thread.  NORM: the last term of a step; the block's part
 // of the squared norms goes to a.parts (summed over each wave, then over the

@@ -16,6 +16,7 @@
 // a thread per site and per pair adding up 1000 realisations took 1.48 ms.
 // One particle: the tile's rows are realisations.
 #include "ctqw_internal.hpp"
+#include "wave_sum.hpp"
 
 namespace ctqw {
 namespace {
@@ -23,21 +24,6 @@ namespace {
 constexpr int kRows = 16;       // rows of a tile: 4 waves x 4
 constexpr int kCols = 128;      // columns: two per lane, 64 apart
 constexpr int kPerWave = kRows / 4;
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_part(double v) {
-    return __builtin_amdgcn_update_dpp(0.0, v, CTRL, ROWS, 0xF, true);
-}
-// Sum over the wave, valid in lane 63.
-__device__ __forceinline__ double wave_sum_last(double v) {
-    v += dpp_part<0x111, 0xF>(v);   // row_shr:1
-    v += dpp_part<0x112, 0xF>(v);   // row_shr:2
-    v += dpp_part<0x114, 0xF>(v);   // row_shr:4
-    v += dpp_part<0x118, 0xF>(v);   // row_shr:8
-    v += dpp_part<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_part<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
 
 template <typename S>
 __device__ __forceinline__ S uniform_entry(const S* table, int index) {

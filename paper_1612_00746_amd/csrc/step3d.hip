@@ -11,6 +11,7 @@
 // 1.46 ms, 5.9 TB/s (one launch for the x3 sums and one for the others took
 // 4.6 ms).
 #include "ctqw_internal.hpp"
+#include "wave_sum.hpp"
 
 namespace ctqw {
 namespace {
@@ -18,21 +19,6 @@ namespace {
 constexpr int kRows3 = 8;                // x2 rows per wave
 constexpr int kTile2 = 4 * kRows3;       // x2 rows of a block
 constexpr int kTile3 = 128;              // x3 columns
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_part(double v) {
-    return __builtin_amdgcn_update_dpp(0.0, v, CTRL, ROWS, 0xF, true);
-}
-// Sum over the wave, valid in lane 63.
-__device__ __forceinline__ double wave_sum_last(double v) {
-    v += dpp_part<0x111, 0xF>(v);   // row_shr:1
-    v += dpp_part<0x112, 0xF>(v);   // row_shr:2
-    v += dpp_part<0x114, 0xF>(v);   // row_shr:4
-    v += dpp_part<0x118, 0xF>(v);   // row_shr:8
-    v += dpp_part<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_part<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
 
 template <typename C>
 __global__ void __launch_bounds__(256) marg3_kernel(Obs3Args a) {
