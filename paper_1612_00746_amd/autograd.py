@@ -5,10 +5,10 @@ diagonal observable L = (1/R) sum_r <psi_r(T)|W|psi_r(T)> of a noisy walk
 whose realisation r has hoppings Jbar + dJ_r and on-site energies
 epsbar + deps_r (fixed noise draws held by ``model``).  The forward pass
 propagates with checkpoints (``ctqw_forward_ckpt``) and evaluates the loss
-(``ctqw_loss``); the backward pass recomputes each checkpoint segment but
-the newest, whose states the forward run kept, and runs the hand-written adjoint kernels (``ctqw_backward``), returning
-dL/dJbar and dL/depsbar scaled by the incoming gradient.  Only argument
-marshalling happens here.
+(``ctqw_loss``); the backward pass recomputes each checkpoint segment (but
+the newest where the forward run kept its states) and runs the hand-written
+adjoint kernels (``ctqw_backward``), returning dL/dJbar and dL/depsbar scaled
+by the incoming gradient.  Only argument marshalling happens here.
 """
 
 from __future__ import annotations

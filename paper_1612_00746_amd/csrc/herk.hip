@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256, 2) herk_c128_kernel(HerkArgs a) {
 int herk_tile(int dtype) { return dtype == 1 ? herk_detail::TS2 : herk_detail::TS; }
 int herk_stage(int dtype) { return dtype == 1 ? herk_detail::KC2 : herk_detail::KC; }
 
-// Bound by the matrix cores: the whole tiles keep them 85 % busy (2.37 GHz).
+// Bound by the matrix cores: the whole tiles keep them 84.5 % busy (2.33 GHz).
 // Two blocks of a whole tile fit a compute unit, 512 the device, and they all
 // take the same time, so whole tiles go in full rounds of 512.  The tiles
 // past the last full round go in quarters while those still take less than a

@@ -18,8 +18,9 @@ ResidentFn kernel_of(const ResidentShape& s) {
 // sums (complex64: and its state) have to fit the 2048 registers x 64 lanes
 // of a compute unit with room to work in: 128 columns (two per lane), except
 // complex128 full grids, where 96 rows is the last size that does not spill
-// heavily.  Which calls of them do is resident_pays' choice.  Times per step against the swept bands of step2d_impl.hpp, 1000
-// realisations (orders 12 complex128, 7 complex64):
+// heavily.  Which calls of such a batch run on chip is resident_pays' choice.
+// Times per step against the swept bands of step2d_impl.hpp, 1000 realisations
+// (orders 12 complex128, 7 complex64):
 //   bosons  N = 128: 90 / 733 us, complex64 43 / 135;  N = 64: 27 / 250, 12 / 46
 //   grid    N = 96: 127 / 284, complex64 41 / 59;  N = 64: 43 / 147, 16 / 33
 //   16 realisations, bosons N = 64: 9 / 153, complex64 5 / 29

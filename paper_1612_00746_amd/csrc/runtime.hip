@@ -571,7 +571,7 @@ ctqw_status build_tables_at(ctqw_plan* p, int room) {
             // Full grids.  A kernel that holds one wave per SIMD (complex64 with 12
             // terms, complex128 from 8) takes a second round for a few items past
             // one per SIMD: round down (us per step rounding up / down: complex64
-            // N = 2000, R = 1, 12 terms 145 / 96; complex128 N = 704, R = 16, 7
+            // N = 2000, R = 1, 12 terms 139 / 87; complex128 N = 704, R = 16, 7
             // terms 158 / 96; N = 256, R = 40, 9 terms 99 / 68).  complex128 at 6
             // and 7 terms, two waves whose FP64 fills a SIMD, likewise.  Where two
             // waves do share a SIMD well, a few items past the target still
