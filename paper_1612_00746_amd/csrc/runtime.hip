@@ -1485,13 +1485,29 @@ ctqw_status collect_timing(ctqw_plan* p) {
     return CTQW_OK;
 }
 
+// What is left of the allocation that holds `at`: false if it is no device
+// allocation of its own.
+bool allocation_left(const void* at, int64_t* left) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void*>(at)) != hipSuccess) {
+        (void)hipGetLastError();   // not known to the runtime: no error of ours
+        return false;
+    }
+    *left = (int64_t)size - (static_cast<const char*>(at) - static_cast<const char*>(base));
+    return *left > 0;
+}
+
 // Whether a state copy between the caller's buffer and `mine` may run as a
-// kernel: device memory of the same device, aligned, apart from `mine`.
-// Anything else (another device's memory, an odd address) is the runtime's.
+// kernel: device memory of the same device in one allocation, aligned, apart
+// from `mine`.  Anything else (another device's memory, an odd address, a range
+// of several mappings) is the runtime's.
 bool kernel_copies(int32_t on_device, const void* theirs, const void* mine, int64_t bytes) {
     if (!on_device || (reinterpret_cast<uintptr_t>(theirs) & 15)) return false;
     const char *a = static_cast<const char*>(theirs), *b = static_cast<const char*>(mine);
     if (a < b + bytes && b < a + bytes) return false;
+    int64_t left = 0;
+    if (!allocation_left(theirs, &left) || left < bytes) return false;
     hipPointerAttribute_t at{}, am{};
     if (hipPointerGetAttributes(&at, theirs) != hipSuccess || hipPointerGetAttributes(&am, mine) != hipSuccess) {
         (void)hipGetLastError();   // not known to the runtime: no error of ours
@@ -1500,20 +1516,17 @@ bool kernel_copies(int32_t on_device, const void* theirs, const void* mine, int6
     return at.type == hipMemoryTypeDevice && am.type == hipMemoryTypeDevice && at.device == am.device;
 }
 
-// A device buffer of the caller's that ends before the state does: the kernel
-// would run past it, where the runtime's copy refuses.
+// A device buffer of the caller's that ends before the state does is refused.
+// (Virtual memory may be mapped piece by piece: the next piece starts where
+// one ends.)
 ctqw_status check_extent(ctqw_plan* p, int32_t on_device, const void* theirs, int64_t bytes) {
     if (!on_device) return CTQW_OK;
-    hipDeviceptr_t base = nullptr;
-    size_t size = 0;
-    if (hipMemGetAddressRange(&base, &size, const_cast<void*>(theirs)) != hipSuccess) {
-        (void)hipGetLastError();   // not an allocation of its own: the copy decides
-        return CTQW_OK;
-    }
-    const int64_t left = (int64_t)size - (static_cast<const char*>(theirs) - static_cast<const char*>(base));
-    if (left < bytes)
-        return fail(p, CTQW_ERR_DEVICE, "the device buffer ends after %lld of the state's %lld bytes", (long long)left,
+    for (int64_t known = 0, left = 0; known < bytes; known += left) {
+        if (allocation_left(static_cast<const char*>(theirs) + known, &left)) continue;
+        if (known == 0) return CTQW_OK;   // the copy decides
+        return fail(p, CTQW_ERR_DEVICE, "the device buffer ends after %lld of the state's %lld bytes", (long long)known,
                     (long long)bytes);
+    }
     return CTQW_OK;
 }
 

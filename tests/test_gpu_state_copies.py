@@ -1,6 +1,7 @@
 """ctqw_set_state / ctqw_get_state on device buffers that end before the state:
 refused before anything is written, whatever the alignment; the state and a
-whole buffer's copies are untouched by the refusal."""
+whole buffer's copies are untouched by the refusal.  Buffers of virtual memory
+mapped in several pieces hold as much as their pieces together."""
 
 import ctypes as C
 
@@ -36,3 +37,46 @@ def test_short_device_buffers_are_refused(N, dtype):
         assert (got, put) == ((0, 0) if skip == 0 else (L.ERR_DEVICE, L.ERR_DEVICE))
         assert np.array_equal(plan.state_numpy(), psi)
     assert hip.hipFree(buf) == 0
+
+
+class AllocationProp(C.Structure):
+    """hipMemAllocationProp of plain device memory."""
+    _fields_ = [("type", C.c_int), ("handle", C.c_int), ("location", C.c_int), ("device", C.c_int),
+                ("win32", C.c_void_p), ("flags", C.c_uint32)]
+
+
+class AccessDesc(C.Structure):
+    _fields_ = [("location", C.c_int), ("device", C.c_int), ("flags", C.c_int)]
+
+
+def test_buffers_mapped_in_pieces():
+    """A state across two mappings is read and written like any other."""
+    N = 600                                            # 5.8 MB of complex128
+    plan = gpu_plan(m=2, statistics="distinguishable", boundary="open", interaction="onsite", dtype="c128",
+                    reals=[(N, np.ones(N - 1), np.zeros(N), 1.0)], dt=0.05, order=4, sites=[1, 2])
+    plan.propagate(3)
+    psi = plan.state_numpy()
+    hip, piece = hip_runtime(), 4 << 20
+    assert piece < psi.nbytes < 2 * piece
+    prop, va, hands = AllocationProp(type=1, location=1), C.c_void_p(), []
+    assert hip.hipMemAddressReserve(C.byref(va), C.c_size_t(2 * piece), C.c_size_t(0), None, C.c_uint64(0)) == 0
+    for i in range(2):
+        h = C.c_void_p()
+        assert hip.hipMemCreate(C.byref(h), C.c_size_t(piece), C.byref(prop), C.c_uint64(0)) == 0
+        assert hip.hipMemMap(C.c_void_p(va.value + i * piece), C.c_size_t(piece), C.c_size_t(0), h, C.c_uint64(0)) == 0
+        hands.append(h)
+    acc = AccessDesc(location=1, flags=3)
+    assert hip.hipMemSetAccess(va, C.c_size_t(2 * piece), C.byref(acc), C.c_size_t(1)) == 0
+    say("case: state copies across two mappings")
+    assert plan.lib.ctqw_get_state(plan.h, va, 1) == 0
+    host = np.empty_like(psi)
+    assert hip.hipMemcpy(host.ctypes.data_as(C.c_void_p), va, C.c_size_t(psi.nbytes), C.c_int(2)) == 0
+    assert np.array_equal(host, psi)
+    plan.propagate(2)
+    assert not np.array_equal(plan.state_numpy(), psi)
+    assert plan.lib.ctqw_set_state(plan.h, va, 1) == 0
+    assert np.array_equal(plan.state_numpy(), psi)
+    for i, h in enumerate(hands):
+        assert hip.hipMemUnmap(C.c_void_p(va.value + i * piece), C.c_size_t(piece)) == 0
+        assert hip.hipMemRelease(h) == 0
+    assert hip.hipMemAddressFree(va, C.c_size_t(2 * piece)) == 0
