@@ -313,7 +313,7 @@ struct LatticeArgs {
     double dt;
 };
 int lattice_max_order(int dtype);
-hipError_t launch_lattice_step(const LatticeArgs& a, int dtype, int order, int cols, bool vec, hipStream_t s);
+hipError_t launch_lattice_step(const LatticeArgs& a, int dtype, int order, int cols, bool vec, bool wide, hipStream_t s);
 hipError_t launch_lattice_norms(const double* part, int32_t per, int32_t R, int32_t steps, double* out, hipStream_t s);
 }  // namespace ctqw
 

@@ -88,9 +88,28 @@ __device__ __forceinline__ void store_c(double re, double im, __amdgpu_buffer_rs
     __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)off, 0, 2);
 }
 
-// rows in flight: n levels and the row entering; even, so that the rows being
-// fetched (two) divide the unrolled sweep of one ring
-__host__ __device__ constexpr int ring_rows(int nt) { return (nt + 2) & ~1; }
+// Rows of the ring, the unrolled block of a sweep: those in flight, n levels
+// and the row entering; even, so that the rows being fetched (two) divide it.
+// A sweep runs whole blocks (leaving one early would cost every block a branch
+// that its registers have to meet at: 5 to 15 % of a long sweep), so short ones
+// may run mostly past their end.  At the orders where the registers and the LDS
+// keep their waves there is a second ring of two rows more, for the sweeps that
+// it covers in fewer rows (us per 8 steps, first ring -> chosen, and the
+// three-row sweeps before; complex128 unless said): 33 x 13, 8 terms, 21 rows
+// in 30 or 24: 170 -> 145 (141); 163 x 12, 6 terms, 18 in 24 or 20: 126 -> 113
+// (108); 249 x 15, 9 terms, 24 in 30 or 24: 187 -> 160 (161); complex64 15 x 15,
+// 8 terms: 140 -> 119 (128); 171 x 4, 1748 realisations, 8 terms: 493 -> 330
+// (445).
+constexpr int kWideFrom = 4, kWideTo = 9;   // orders of the second ring
+__host__ __device__ constexpr int ring_rows(int nt, bool wide) { return ((nt + 2) & ~1) + (wide ? 2 : 0); }
+// rows that a sweep of `rows` runs with a ring, and whether the second's are fewer
+inline int64_t swept_rows(int64_t rows, int nt, bool wide) {
+    const int64_t block = ring_rows(nt, wide);
+    return (rows + block - 1) / block * block;
+}
+inline bool wide_ring(int64_t rows, int nt) {
+    return nt >= kWideFrom && nt <= kWideTo && swept_rows(rows, nt, true) < swept_rows(rows, nt, false);
+}
 __host__ __device__ constexpr int mpos(int x, int w) { return ((x % w) + w) % w; }
 __host__ __device__ constexpr double inv_fact(int j) {
     double f = 1.0;
@@ -258,13 +277,12 @@ __device__ __forceinline__ void level(const T (&xr)[P], const T (&xi)[P], const 
 }
 
 // LDS of one wave: a ring of table rows, {e, jr} and {jd} of every lane.
-template <typename T, int NT, int P>
-constexpr size_t wave_lds() { return (size_t)ring_rows(NT) * 64 * 3 * P * sizeof(T); }
+template <typename T, int P>
+constexpr size_t wave_lds(int ring) { return (size_t)ring * 64 * 3 * P * sizeof(T); }
 
-template <typename T, int NT, int P, bool VEC>
+template <typename T, int NT, int P, bool VEC, int WA>
 __global__ void __launch_bounds__(256, 2) lattice_kernel(LatticeArgs a) {
     using C = typename Cplx<T>::type;
-    constexpr int WA = ring_rows(NT);
     constexpr int W = 64 * P, H = halo_of(NT, P);
     constexpr int PF = 2;   // rows fetched ahead
     constexpr int AHEAD = P == 2 ? 1 : (sizeof(T) == 4 ? 3 : 2);   // levels whose tables are read ahead
@@ -285,8 +303,8 @@ __global__ void __launch_bounds__(256, 2) lattice_kernel(LatticeArgs a) {
     extern __shared__ char lds_raw[];
     struct alignas(2 * P * sizeof(T)) EJ { T e[P], jr[P]; };
     struct alignas(P * sizeof(T)) JD { T d[P]; };
-    EJ* const ring_ej = reinterpret_cast<EJ*>(lds_raw + wv * wave_lds<T, NT, P>()) + lane;
-    JD* const ring_jd = reinterpret_cast<JD*>(lds_raw + wv * wave_lds<T, NT, P>() + (size_t)WA * 64 * sizeof(EJ)) + lane;
+    EJ* const ring_ej = reinterpret_cast<EJ*>(lds_raw + wv * wave_lds<T, P>(WA)) + lane;
+    JD* const ring_jd = reinterpret_cast<JD*>(lds_raw + wv * wave_lds<T, P>(WA) + (size_t)WA * 64 * sizeof(EJ)) + lane;
 
     // this lane's columns (an open axis has no bond past its last node)
     bool outv[P];
@@ -470,25 +488,39 @@ struct Kernel {
     void (*fn)(LatticeArgs) = nullptr;
     size_t lds = 0;
 };
+template <typename T, int NT, int P, bool VEC, bool WIDE>
+Kernel kernel_of() {
+    constexpr int WA = ring_rows(NT, WIDE);
+    return Kernel{&lattice_kernel<T, NT, P, VEC, WA>, 4 * wave_lds<T, P>(WA)};
+}
 template <typename T, int P, bool VEC, int... Ns>
 Kernel pick(int order, std::integer_sequence<int, Ns...>) {
     Kernel k;
-    ((k = (order == Ns + 1) ? Kernel{&lattice_kernel<T, Ns + 1, P, VEC>, 4 * wave_lds<T, Ns + 1, P>()} : k), ...);
+    ((k = (order == Ns + 1) ? kernel_of<T, Ns + 1, P, VEC, false>() : k), ...);
     return k;
+}
+template <typename T, int P, bool VEC, int... Ns>
+Kernel pick_wide(int order, std::integer_sequence<int, Ns...>) {
+    Kernel k;
+    ((k = (order == Ns + kWideFrom) ? kernel_of<T, Ns + kWideFrom, P, VEC, true>() : k), ...);
+    return k;
+}
+template <typename T, int P, bool VEC, int MAX>
+Kernel pick(int order, bool wide) {
+    return wide ? pick_wide<T, P, VEC>(order, std::make_integer_sequence<int, kWideTo - kWideFrom + 1>{})
+                : pick<T, P, VEC>(order, std::make_integer_sequence<int, MAX>{});
 }
 
 }  // namespace lattice_detail
 
 int lattice_max_order(int dtype) { return dtype == 1 ? kLatticeMaxOrderC128 : kLatticeMaxOrderC64; }
 
-hipError_t launch_lattice_step(const LatticeArgs& a, int dtype, int order, int cols, bool vec, hipStream_t s) {
+hipError_t launch_lattice_step(const LatticeArgs& a, int dtype, int order, int cols, bool vec, bool wide, hipStream_t s) {
     using namespace lattice_detail;
-    constexpr auto o64 = std::make_integer_sequence<int, kLatticeMaxOrderC64>{};
-    constexpr auto o2 = std::make_integer_sequence<int, kLatticePairOrder>{};
-    constexpr auto o128 = std::make_integer_sequence<int, kLatticeMaxOrderC128>{};
-    const Kernel k = dtype == 1 ? pick<double, 1, false>(order, o128)
-                                : (cols == 1 ? pick<float, 1, false>(order, o64)
-                                             : (vec ? pick<float, 2, true>(order, o2) : pick<float, 2, false>(order, o2)));
+    const Kernel k = dtype == 1 ? pick<double, 1, false, kLatticeMaxOrderC128>(order, wide)
+                     : cols == 1 ? pick<float, 1, false, kLatticeMaxOrderC64>(order, wide)
+                     : vec       ? pick<float, 2, true, kLatticePairOrder>(order, wide)
+                                 : pick<float, 2, false, kLatticePairOrder>(order, wide);
     if (!k.fn || (dtype == 1 && cols != 1)) return hipErrorInvalidValue;
     if (k.lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k.fn),
@@ -564,13 +596,12 @@ ctqw_status lattice_layout(int32_t Lx, int32_t Ly, int32_t R, int32_t dtype, int
     // 144 whole; 64 rings of 97 x 65, complex128, 9 terms: 30 and 51.)
     {
         constexpr int64_t kSimds = 1024;
-        const int64_t block = lattice_detail::ring_rows(order);
         auto cost = [&](int64_t items, int64_t sg, int cols) {
             const int64_t steps = (Ly + sg - 1) / sg + (sg > 1 ? 2 * order : 0) + order;
             const int64_t w = (items * sg + kSimds - 1) / kSimds;
             const int64_t row = cols == 2 ? 32 * w : (dtype == CTQW_C64 ? std::max<int64_t>(22, 15 * w)
                                                                         : std::max<int64_t>(30, 21 * w));
-            return (steps + block - 1) / block * block * row;
+            return lattice_detail::swept_rows(steps, order, false) * row;
         };
         int64_t best = INT64_MAX;
         for (int cols : {1, 2}) {
@@ -646,6 +677,11 @@ extern "C" ctqw_status ctqw_lattice_evolve(int32_t Lx, int32_t Ly, int32_t perio
     const bool vec = l.cols == 2 && Lx % 2 == 0 &&
                      ((reinterpret_cast<uintptr_t>(psi) | reinterpret_cast<uintptr_t>(Jx) | reinterpret_cast<uintptr_t>(Jy) |
                        reinterpret_cast<uintptr_t>(eps)) & 15) == 0;
+    // the rows of the longest sweep: output rows, the halo above and below (on an
+    // open axis to its ends only) and the pipeline's depth
+    const int out_rows = (Ly + l.segs - 1) / l.segs, halos = std::min(l.segs - 1, 2);
+    const int64_t sweep = a.py ? out_rows + 2 * order : std::min(out_rows + halos * order, Ly);
+    const bool wide = lattice_detail::wide_ring(sweep + order, order);
     double* const part = reinterpret_cast<double*>(ws + l.part);
     const int64_t bytes = (int64_t)Lx * Ly * R * (d ? 16 : 8);
     void* buf[2] = {psi, ws + l.state};
@@ -654,7 +690,7 @@ extern "C" ctqw_status ctqw_lattice_evolve(int32_t Lx, int32_t Ly, int32_t perio
         a.psi_in = buf[k & 1];
         a.psi_out = buf[(k + 1) & 1];
         a.norm_part = part + (int64_t)held * a.n_items;
-        if ((e = launch_lattice_step(a, d, order, l.cols, vec, s)) != hipSuccess) return hip_fail(e);
+        if ((e = launch_lattice_step(a, d, order, l.cols, vec, wide, s)) != hipSuccess) return hip_fail(e);
         if (!norms) continue;
         ++held;
         if (held == l.held || k + 1 == n_steps) {
