@@ -94,8 +94,8 @@ __device__ __forceinline__ void store_c(double re, double im, __amdgpu_buffer_rs
 // that its registers have to meet at: 5 to 15 % of a long sweep), so short ones
 // may run mostly past their end.  At the orders where the registers and the LDS
 // keep their waves there is a second ring of two rows more, for the sweeps that
-// it covers in fewer rows (us per 8 steps, first ring -> chosen, and the
-// three-row sweeps before; complex128 unless said): 33 x 13, 8 terms, 21 rows
+// it covers in fewer rows (us per 8 steps, first ring -> chosen by itself, and
+// the three-row sweeps before; complex128 unless said): 33 x 13, 8 terms, 21 rows
 // in 30 or 24: 170 -> 145 (141); 163 x 12, 6 terms, 18 in 24 or 20: 126 -> 113
 // (108); 249 x 15, 9 terms, 24 in 30 or 24: 187 -> 160 (161); complex64 15 x 15,
 // 8 terms: 140 -> 119 (128); 171 x 4, 1748 realisations, 8 terms: 493 -> 330
@@ -285,6 +285,11 @@ __global__ void __launch_bounds__(256, 2) lattice_kernel(LatticeArgs a) {
     using C = typename Cplx<T>::type;
     constexpr int W = 64 * P, H = halo_of(NT, P);
     constexpr int PF = 2;   // rows fetched ahead
+    // complex128: the bonds to the left shifted once per row instead of in every
+    // level (two moves of 28 instructions) where the ring of them costs no wave
+    // per SIMD (13 x 56, 4190 realisations, 6 terms, 8 steps: 831 -> 796 us;
+    // order 5 would fall from three waves to two and take 10 % more)
+    constexpr bool KEEPL = sizeof(T) == 8 && NT >= 4 && NT <= 8 && NT != 5;
     constexpr int AHEAD = P == 2 ? 1 : (sizeof(T) == 4 ? 3 : 2);   // levels whose tables are read ahead
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -358,6 +363,7 @@ __global__ void __launch_bounds__(256, 2) lattice_kernel(LatticeArgs a) {
     T ur[NT][P], ui[NT][P];             // level j: what its next row starts from
     T pr[WA][P], pi[WA][P];             // psi of the rows in flight
     T tr[WA][P], ti[WA][P];             // their summed terms
+    T lr[KEEPL ? WA : 1];               // the bonds to the left of their first columns
 #pragma unroll
     for (int p = 0; p < P; ++p) {
 #pragma unroll
@@ -365,6 +371,8 @@ __global__ void __launch_bounds__(256, 2) lattice_kernel(LatticeArgs a) {
 #pragma unroll
         for (int w = 0; w < WA; ++w) pr[w][p] = pi[w][p] = tr[w][p] = ti[w][p] = T(0);
     }
+#pragma unroll
+    for (int w = 0; w < (KEEPL ? WA : 1); ++w) lr[w] = T(0);
     {
         EJ z{};
         JD zd{};
@@ -402,6 +410,7 @@ __global__ void __launch_bounds__(256, 2) lattice_kernel(LatticeArgs a) {
                 jd.d[p] = dt * fd[sp][p];
             }
             if (VEC) ej.jr[P - 1] = last_pair ? T(0) : ej.jr[P - 1];
+            if (KEEPL) lr[w] = lane_left(ej.jr[P - 1]);
             fetch(i + PF, sp);
             // tables of the next AHEAD levels' rows (of row i - j: te, the bonds
             // below it: td), read while the levels before them run: a level of
@@ -424,7 +433,7 @@ __global__ void __launch_bounds__(256, 2) lattice_kernel(LatticeArgs a) {
                 const EJ ej_next = te[j % AHEAD];
                 read(j + AHEAD);
                 __builtin_amdgcn_sched_barrier(0);
-                const T jl = lane_left(ej.jr[P - 1]);
+                const T jl = KEEPL ? lr[KEEPL ? mpos(u - j + 1, WA) : 0] : lane_left(ej.jr[P - 1]);
                 const T cr = static_cast<T>(rot_re(j) * inv_fact(j)), ci = static_cast<T>(rot_im(j) * inv_fact(j));
                 T yr[P], yi[P];
                 level<T, P>(xr, xi, ej.e, ej.jr, jl, jd.d, below.d, sr[j - 1], si[j - 1], ur[j - 1], ui[j - 1], yr, yi);
