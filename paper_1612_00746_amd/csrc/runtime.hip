@@ -436,6 +436,43 @@ int on_chip_layout(const ctqw_problem& pr) {
     return pr.boundary == CTQW_PERIODIC ? kResRing : kResFull;
 }
 
+// Whether steps of an order that only one column per lane is compiled for, in
+// a plan of two, run there in one pass, or in passes of a few terms, which move
+// the state once each and whose bands are not split, but sweep fewer rows past
+// the band's end and recompute fewer columns of halo.  One pass for up to one
+// band per SIMD (its rows are split), except one particle with two a-priori
+// orders: those are two launches, and the passes run both (complex128, orders 7
+// and 8, N = 26, R = 144: 17 us in passes, 20 in two launches); of more,
+//   complex64 to 11 terms: two waves per SIMD, one pass always;
+//   one particle: a band has one row and the rest of its sweep is the
+//     pipeline's depth, so passes;
+//   two: one pass from the sizes on whose rows outweigh that depth.  The
+//     complex128 triangle's kernel of 12 terms spills.
+// us of a step chunked / in one pass.  Two particles, N = 300: full grid
+// complex128 order 12, R = 1 449 / 58, 60 498 / 147, 400 1424 / 752; complex64
+// order 10, R = 800 1251 / 522; bosons complex64 order 10, R = 1000 1265 / 729,
+// complex128 order 9, R = 600 1434 / 754, order 12 R = 60 622 / 235, 1000 1436 /
+// 1461; N = 64, R = 2500 352 / 425; grid N = 20, R = 9000, order 11 205 / 277,
+// N = 32 354 / 361.  One particle, complex128: N = 300, order 9, R = 100 22 / 15,
+// 1600 73 / 103, order 12 18 / 22 and 73 / 138; N = 4000, R = 400, order 12 182 /
+// 497; complex64 order 12 268 / 373, order 11 267 / 166.
+bool one_pass_pays(const ctqw_plan* p, int dtype, int order) {
+    const ctqw_problem& pr = p->prob;
+    if (dtype == 0 && order <= 11) return true;
+    int64_t bands = 0, sites = 0;
+    bool one_order = true;
+    for (int64_t r = 0; r < pr.R; ++r) {
+        one_order = one_order && p->order[r] == order;
+        const int inner = pr.boundary == CTQW_PERIODIC ? p->N[r] : std::max(1, p->N[r] - 2 * order);
+        bands += (inner + 63 - 2 * order) / (64 - 2 * order);
+        sites += p->N[r];
+    }
+    const int64_t mean = sites / std::max<int64_t>(1, pr.R);
+    const bool spills = dtype == 1 && pr.m == 2 && pr.statistics != CTQW_DISTINGUISHABLE && order == 12;
+    if (bands <= kSplitTarget) return pr.m == 1 ? one_order : !spills || mean > 20;
+    return pr.m == 2 && mean > (spills ? 192 : (dtype == 1 ? 24 : 8));
+}
+
 // How much workspace a layout may take for speed alone.
 enum Roominess { kRoomy = 0, kOneSlot = 1, kFewSegments = 2 };
 
@@ -445,14 +482,9 @@ ctqw_status build_tables_at(ctqw_plan* p, int room) {
     int maxn = 0;
     for (int64_t r = 0; r < pr.R; ++r) maxn = std::max(maxn, p->order[r]);
     const int dtype = pr.dtype == CTQW_C128 ? 1 : 0;
-    // Orders that only one column per lane is compiled for run there in one
-    // pass, whatever the request (passes of a few terms move the state once
-    // each, and their bands are not split).  us per step at N = 300, chunked ->
-    // one pass: full grid complex128 order 12, R = 1 449 -> 58, 60 498 -> 147,
-    // 400 1424 -> 752; complex64 order 10, R = 800 1251 -> 522; bosons complex64
-    // order 10, R = 1000 1265 -> 729, complex128 order 9, R = 600 1434 -> 754,
-    // order 12 the one tie (1436 / 1461; R = 60 622 -> 235).
-    if (pr.m != 3 && step_levels_bucket(dtype, P, maxn) < 0 && step_levels_bucket(dtype, 1, maxn) >= 0) P = 1;
+    if (pr.m != 3 && step_levels_bucket(dtype, P, maxn) < 0 && step_levels_bucket(dtype, 1, maxn) >= 0 &&
+        (room > kRoomy || one_pass_pays(p, dtype, maxn)))
+        P = 1;
     const int W = 64 * P;
     const int fused = pr.m == 3 ? maxn : step_levels_bucket(dtype, P, maxn);
     // chunked passes when the order has no fused pipeline, or on request
