@@ -1533,9 +1533,11 @@ bool allocation_left(const void* at, int64_t* left) {
 // Whether a state copy between the caller's buffer and `mine` may run as a
 // kernel: device memory of the same device in one allocation, aligned, apart
 // from `mine`.  Anything else (another device's memory, an odd address, a range
-// of several mappings) is the runtime's.
+// of several mappings) is the runtime's, and so is a state of up to 128 MB,
+// which it copies as fast (launch_copy) without what is asked here (1 us).
 bool kernel_copies(int32_t on_device, const void* theirs, const void* mine, int64_t bytes) {
-    if (!on_device || (reinterpret_cast<uintptr_t>(theirs) & 15)) return false;
+    constexpr int64_t kRuntimes = int64_t(128) << 20;
+    if (!on_device || bytes <= kRuntimes || (reinterpret_cast<uintptr_t>(theirs) & 15)) return false;
     const char *a = static_cast<const char*>(theirs), *b = static_cast<const char*>(mine);
     if (a < b + bytes && b < a + bytes) return false;
     int64_t left = 0;
