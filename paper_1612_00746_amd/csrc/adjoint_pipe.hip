@@ -65,8 +65,8 @@ hipError_t launch_adj_pipe(const AdjPipeArgs& a, hipStream_t s) {
     // Two Horner levels, distinguishable, N = 129, complex128, 72 blocks: 22.0
     // us in four segments, 19.6 in eight.  Three Horner levels, two bosons,
     // N = 256, complex64, 2560 blocks: 223 us in four, 249 in eight.
-    // (One particle's single row is one segment's.)
-    const int segs = a.layout != 0 && (int64_t)bands * a.R <= 256 ? kSweepSegsMax : kSweepSegs;
+    // One particle's single row is one wave's.
+    const int segs = a.layout == 0 ? 1 : ((int64_t)bands * a.R <= 256 ? kSweepSegsMax : kSweepSegs);
     hipLaunchKernelGGL(fn, g, dim3((unsigned)(64 * segs)), 0, s, a);
     return hipGetLastError();
 }

@@ -34,8 +34,8 @@
 // realisations (72 bands): passes of two Horner levels 30 -> 19.6 us, of four
 // forward levels 28 -> 18.5 us, where latency is what is left.
 //
-// Contractions.  Full grid (distinguishable particles; one particle is the
-// one-row case): the column parts of bond c and site c are sums over the
+// Contractions.  Full grid (distinguishable particles; of one particle only the
+// column parts): the column parts of bond c and site c are sums over the
 // rows, kept per lane; the row parts of bond q and site q are sums over the
 // columns, reduced across the wave for three rows at a time into one
 // partial per band.
@@ -160,6 +160,62 @@ __device__ __forceinline__ void contract(T mr, T mi, T dr, T di, T rr, T ri, T v
     }
 }
 
+// One particle: a realisation is a single row, so the levels are K stencils of
+// the same lanes and a block is one wave, with every load issued at the start.
+// off, off_out: the lane's offset in the row to read and to write (past the end
+// where nothing is stored).  As a sweep of 1 + K rows the passes took 3.3 to 4.2
+// us in complex128, nearly all of it latency and code fetched once: 259 rings of
+// 30 nodes, complex128, 9 steps, 435 -> 367 us per gradient; 66 chains of 242, 418
+// -> 360.
+template <typename T, int K, bool CON>
+__device__ __forceinline__ void one_row(const AdjPipeArgs& a, const RealDev& rd, int r, int cw, bool out, uint32_t off,
+                                        uint32_t off_out, T d, T jl, T jr, bool has_bond) {
+    using C = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
+    auto rsrc = [&](const void* base) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<C*>(reinterpret_cast<const C*>(base)) + rd.state_off, 0,
+                                                 base ? (int)((uint32_t)rd.N * (uint32_t)sizeof(C)) : 0,
+                                                 kRawBufferWord3);
+    };
+    const C x = load_c(rsrc(a.x), off, (C*)nullptr);
+    C z, v[CON ? K : 1];
+    double gj = 0.0, ge = 0.0;
+    int64_t o = 0;
+    if constexpr (CON) {
+        z = load_c(rsrc(a.z), off, (C*)nullptr);
+#pragma unroll
+        for (int l = 0; l < K; ++l) v[l] = load_c(rsrc(a.v[l]), off, (C*)nullptr);
+        if (out) {
+            o = a.site_off[r] + cw;
+            gj = a.gJ[o];
+            ge = a.gE[o];
+        }
+    }
+    const T xs = static_cast<T>(a.xs);
+    T mr = xs * x.x, mi = xs * x.y;
+    double bond = 0.0, site = 0.0;
+#pragma unroll
+    for (int l = 1; l <= K; ++l) {
+        T yr, yi, rr = T(0), ri = T(0);
+        stencil<T, false, CON>(mr, mi, T(0), T(0), T(0), T(0), d, T(0), T(0), jl, jr, yr, yi, rr, ri);
+        if constexpr (CON) {
+            const T cz = static_cast<T>(a.cz[l]);
+            yr = fma(cz, z.x, yr);
+            yi = fma(cz, z.y, yi);
+            T s0, hb, vb;
+            contract(mr, mi, T(0), T(0), rr, ri, v[l - 1].x, v[l - 1].y, T(0), T(0), s0, hb, vb);
+            site += (double)s0;
+            bond += (double)hb;
+        }
+        if (!CON || l == K) store_c(yr, yi, rsrc(a.y[l - 1]), off_out);
+        mr = yr;
+        mi = yi;
+    }
+    if (CON && out) {
+        a.gJ[o] = gj + (has_bond ? bond : 0.0);
+        a.gE[o] = ge + site;
+    }
+}
+
 template <typename T, int K, int LAY, bool PER, bool CON>
 __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs a) {
     using C = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
@@ -168,7 +224,7 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
     static_assert(K >= 1 && K <= kPipeMaxLevels, "levels per pass");
     static_assert(!(PER && LAY == 2), "no triangle on a ring");
     constexpr bool periodic = PER;          // columns on a ring
-    constexpr bool rper = PER && LAY != 0;  // rows on a ring (one particle: a single row)
+    constexpr bool rper = PER;              // rows on a ring
     constexpr bool tri = LAY == 2;
 
     // Consecutive blocks go to the XCDs in turn: a realisation's bands are
@@ -178,7 +234,7 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
     const int w = blockIdx.x >> 3;
     if (r >= a.R) return;   // whole block, before the barrier
     const RealDev rd = a.reals[r];
-    const int N = rd.N, rows = LAY == 0 ? 1 : rd.rows;
+    const int N = rd.N, rows = rd.rows;
     // Bands are laid from the chain's end: band w outputs [hi - W, hi),
     // hi = N - W (nbr - 1 - w), the first band the rest.
     const int nbr = (N + W - 1) / W;
@@ -205,6 +261,11 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
     const T jr = (inb && (periodic || c < N - 1)) ? Jc[cw] : T(0);
     const T ec = inb ? Ec[cw] : T(0);
     const bool has_bond_c = periodic || c < N - 1;
+    if constexpr (LAY == 0) {
+        const uint32_t off = (uint32_t)cw * (uint32_t)sizeof(C);
+        one_row<T, K, CON>(a, rd, r, cw, out, inb ? off : kPastEnd, out ? off : kPastEnd, ec, jl, jr, has_bond_c);
+        return;
+    }
 
     // rows holding a stored amplitude of this window, split into one segment
     // per wave; the sweep runs K rows beyond the segment on either side
@@ -294,7 +355,7 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const int q = min(qn, last);
-            j[k] = LAY == 0 ? T(0) : Jr[q];
+            j[k] = Jr[q];
             e[k] = Er[q];
             qn = next_row(qn);
         }
@@ -331,7 +392,7 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
     const int j_row = lane >> 4;
     auto holds_row = [&](int s) { return (lane & 7) == 0 && j_row < 3 && s >= o_lo && s < o_hi; };
     double g_old = 0.0;
-    if (CON && LAY != 0) {
+    if (CON) {
         const int s = -K + j_row;
         if (holds_row(s)) g_old = g_row[s_lo + s];
     }
@@ -400,17 +461,15 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
             }
             if constexpr (CON) {
                 // row i - K is complete; its slot takes row i
-                if (LAY != 0) {
-                    const bool diag = tri && cw == qi - K;
-                    batch[2 * mpos(u, 3)] = (double)(out ? rpv[mpos(u - K, U)] : T(0));
-                    batch[2 * mpos(u, 3) + 1] = (double)((out && !diag) ? rps[mpos(u - K, U)] : T(0));
-                    if (mpos(u, 3) == 2) {
-                        // lane 8 j ends with the wave's sum of batch[j]
-                        const double t = reduce8(batch, lane);
-                        const int sr = i - K - 2 + j_row;
-                        if (holds_row(sr)) g_row[s_lo + sr] = g_old + f * t;
-                        if (holds_row(sr + 3)) g_old = g_row[s_lo + sr + 3];
-                    }
+                const bool diag = tri && cw == qi - K;
+                batch[2 * mpos(u, 3)] = (double)(out ? rpv[mpos(u - K, U)] : T(0));
+                batch[2 * mpos(u, 3) + 1] = (double)((out && !diag) ? rps[mpos(u - K, U)] : T(0));
+                if (mpos(u, 3) == 2) {
+                    // lane 8 j ends with the wave's sum of batch[j]
+                    const double t = reduce8(batch, lane);
+                    const int sr = i - K - 2 + j_row;
+                    if (holds_row(sr)) g_row[s_lo + sr] = g_old + f * t;
+                    if (holds_row(sr + 3)) g_old = g_row[s_lo + sr + 3];
                 }
                 vo[mpos(u + 3, U)] = row_off(qx, i + 3 >= o_lo && i + 3 <= o_hi && i + 3 < nsweep, dead);
             }
@@ -422,10 +481,10 @@ __global__ void __launch_bounds__(64 * kSweepSegsMax, 2) pipe_kernel(AdjPipeArgs
                 dd = dd < 0 ? -dd : dd;
                 if (periodic && N - dd < dd) dd = N - dd;
                 T d = ge[u] + ec;
-                if (LAY != 0 && dd == want) d += Udt;
+                if (dd == want) d += Udt;
                 cd[mpos(u, U)] = (live && stored) ? d : T(0);
                 // the bond to row i + 1: none below the grid or past the sweep
-                const T below = (LAY != 0 && i + 1 < nsweep) ? gj[u] : T(0);
+                const T below = i + 1 < nsweep ? gj[u] : T(0);
                 if constexpr (tri) {
                     const bool diag = cw == qi;
                     cu[mpos(u, U)] = stored ? (diag ? above + jl : above) : T(0);
