@@ -215,7 +215,7 @@ def test_adjoint_passes_of_the_largest_batches(recorder):
         assert_launchable(grids[0])
         # whole groups of eight realisations, every band of each
         assert grids[0][0] * grids[0][1] == (R + 7) // 8 * 8 * rest["bands"]
-        assert grids[0][3] == 256   # one particle's row is one wave's work: no eight waves for small batches
+        assert grids[0][3] == 64   # one particle's row is one wave's work
 
 
 def test_graph_terms_of_many_small_graphs(recorder):
