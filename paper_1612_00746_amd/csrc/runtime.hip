@@ -440,9 +440,10 @@ int on_chip_layout(const ctqw_problem& pr) {
 // a plan of two, run there in one pass, or in passes of a few terms, which move
 // the state once each and whose bands are not split, but sweep fewer rows past
 // the band's end and recompute fewer columns of halo.  One pass for up to one
-// band per SIMD (its rows are split), except one particle with two a-priori
-// orders: those are two launches, and the passes run both (complex128, orders 7
-// and 8, N = 26, R = 144: 17 us in passes, 20 in two launches); of more,
+// band per SIMD (its rows are split), except one particle, or two on up to 32
+// sites, with two a-priori orders: those are two launches, and the passes run
+// both (complex128, one particle of orders 7 and 8, N = 26, R = 144: 17 us in
+// passes, 20 in two launches; two particles, N = 7, R = 449: 36 and 45); of more,
 //   complex64 to 11 terms: two waves per SIMD, one pass always;
 //   one particle: a band has one row and the rest of its sweep is the
 //     pipeline's depth, so passes;
@@ -469,7 +470,7 @@ bool one_pass_pays(const ctqw_plan* p, int dtype, int order) {
     }
     const int64_t mean = sites / std::max<int64_t>(1, pr.R);
     const bool spills = dtype == 1 && pr.m == 2 && pr.statistics != CTQW_DISTINGUISHABLE && order == 12;
-    if (bands <= kSplitTarget) return pr.m == 1 ? one_order : !spills || mean > 20;
+    if (bands <= kSplitTarget) return pr.m == 1 ? one_order : mean > (one_order ? (spills ? 20 : 0) : 32);
     return pr.m == 2 && mean > (spills ? 192 : (dtype == 1 ? 24 : 8));
 }
 

@@ -1,7 +1,8 @@
 """Two columns per lane asked for at an order that only one column per lane is
 compiled for: one pass over wide bands, or passes of a few terms over bands
 with little halo (56 output columns of 64 in complex128, 48 in complex64),
-whichever the batch's sizes make the faster.  The number of bands tells."""
+whichever the batch's sizes make the faster.  The number of bands and the
+workspace tell."""
 
 import os
 
@@ -23,7 +24,7 @@ def bands(m, N, R, order, dtype, stat="distinguishable", boundary="periodic", J=
     plan.set_launch(cols_per_lane=2, row_segments=1, **launch)
     bonds = N - (boundary == "open")
     plan.set_params(np.repeat(np.broadcast_to(J, R), bonds), np.zeros(R * N), np.ones(R))
-    return plan.work_items()[0] / R, plan.orders()
+    return (plan.work_items()[0] / R, plan.sizes()[1]), plan.orders()
 
 
 @pytest.mark.parametrize("m,N,R,order,dtype,stat,passes", [
@@ -41,11 +42,14 @@ def test_passes_where_they_are_faster(m, N, R, order, dtype, stat, passes):
     assert (got == whole) == passes, (got, whole)
 
 
-@pytest.mark.parametrize("J,passes", [(1.4, False), (np.array([1.4, 1.4, 1.0, 1.4]), True)])
-def test_two_orders_of_one_particle(J, passes):
+@pytest.mark.parametrize("m,N,J,passes", [
+    (1, 300, 1.4, False), (1, 300, np.array([1.4, 1.4, 1.0, 1.4]), True),
+    (2, 30, 1.0, False), (2, 30, np.array([1.0, 0.6, 1.0, 1.0]), True), (2, 60, np.array([1.0, 0.6, 1.0, 1.0]), False),
+])
+def test_two_orders(m, N, J, passes):
     """Two a-priori orders are two launches of one pass each, so a small batch
-    runs them in passes."""
-    got, orders = bands(1, 300, 4, 0, "c128", J=J)
-    whole, _ = bands(1, 300, 4, 0, "c128", J=J, chunked=1)
-    assert orders.max() >= 8 and (orders.min() < orders.max()) == passes
+    of short sweeps runs them in passes."""
+    got, orders = bands(m, N, 4, 0, "c128", J=J)
+    whole, _ = bands(m, N, 4, 0, "c128", J=J, chunked=1)
+    assert orders.max() >= 8 and (orders.min() < orders.max()) == (np.ndim(J) > 0)
     assert (got == whole) == passes, (got, whole, orders)
