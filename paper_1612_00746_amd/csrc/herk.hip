@@ -288,12 +288,16 @@ int herk_stage(int dtype) { return dtype == 1 ? herk_detail::KC2 : herk_detail::
 // two bosons, R = 1000, N = 128 (2145 tiles, 97 past four rounds) 2.46 ->
 // 2.34 ms, N = 64 (153 tiles) 0.344 -> 0.267, N = 32 (15 tiles) 0.323 ->
 // 0.127; R = 500, N = 101 (349 past a round) 0.621 -> 0.574.  complex128:
-// R = 1000, N = 32 0.203 -> 0.106 ms.
+// R = 1000, N = 32 0.203 -> 0.106 ms.  After whole rounds that is a second launch,
+// 3 us, which few realisations do not win back (us of a call, all whole -> with
+// quarters: complex128 N = 66, 118 tiles past a round, R = 24 59.6 -> 63.7, 128
+// 96.1 -> 96.2, 256 145.6 -> 142.8; complex64 N = 101 R = 16 101.0 -> 104.6, 24
+// 117.2 -> 116.8).
 hipError_t launch_herk(const HerkArgs& a, int dtype, hipStream_t s) {
     if (a.n_tiles <= 0) return hipSuccess;
     constexpr int64_t kRound = 512, kQuarters = 384;
     int64_t tail = a.n_tiles % kRound;
-    if (tail > kQuarters) tail = 0;
+    if (tail > kQuarters || (a.n_tiles > kRound && a.Rp < (dtype == 1 ? 128 : 32))) tail = 0;
     HerkArgs whole = a, quarter = a;
     whole.tile0 = 0;
     whole.n_tiles = a.n_tiles - tail;
