@@ -440,10 +440,11 @@ int on_chip_layout(const ctqw_problem& pr) {
 // a plan of two, run there in one pass, or in passes of a few terms, which move
 // the state once each and whose bands are not split, but sweep fewer rows past
 // the band's end and recompute fewer columns of halo.  One pass for up to one
-// band per SIMD (its rows are split), except one particle, or two on up to 32
+// band per SIMD (its rows are split), except one particle, or two on up to 48
 // sites, with two a-priori orders: those are two launches, and the passes run
 // both (complex128, one particle of orders 7 and 8, N = 26, R = 144: 17 us in
-// passes, 20 in two launches; two particles, N = 7, R = 449: 36 and 45); of more,
+// passes, 20 in two launches; two particles, N = 7, R = 449: 36 and 45, N = 45,
+// R = 900 103 and 114, N = 54 115 and 114); of more,
 //   complex64 to 11 terms: two waves per SIMD, one pass always;
 //   one particle: a band has one row and the rest of its sweep is the
 //     pipeline's depth, so passes;
@@ -454,7 +455,8 @@ int on_chip_layout(const ctqw_problem& pr) {
 // order 10, R = 800 1251 / 522; bosons complex64 order 10, R = 1000 1265 / 729,
 // complex128 order 9, R = 600 1434 / 754, order 12 R = 60 622 / 235, 1000 1436 /
 // 1461; N = 64, R = 2500 352 / 425; grid N = 20, R = 9000, order 11 205 / 277,
-// N = 32 354 / 361.  One particle, complex128: N = 300, order 9, R = 100 22 / 15,
+// N = 32 354 / 361; two orders: grid N = 29, R = 1630 93 / 112, N = 64, R = 1600
+// alike; bosons N = 80, R = 900 218 / 268.  One particle, complex128: N = 300, order 9, R = 100 22 / 15,
 // 1600 73 / 103, order 12 18 / 22 and 73 / 138; N = 4000, R = 400, order 12 182 /
 // 497; complex64 order 12 268 / 373, order 11 267 / 166.
 bool one_pass_pays(const ctqw_plan* p, int dtype, int order) {
@@ -469,9 +471,9 @@ bool one_pass_pays(const ctqw_plan* p, int dtype, int order) {
         sites += p->N[r];
     }
     const int64_t mean = sites / std::max<int64_t>(1, pr.R);
-    const bool spills = dtype == 1 && pr.m == 2 && pr.statistics != CTQW_DISTINGUISHABLE && order == 12;
-    if (bands <= kSplitTarget) return pr.m == 1 ? one_order : mean > (one_order ? (spills ? 20 : 0) : 32);
-    return pr.m == 2 && mean > (spills ? 192 : (dtype == 1 ? 24 : 8));
+    const bool tri = pr.statistics != CTQW_DISTINGUISHABLE, spills = dtype == 1 && pr.m == 2 && tri && order == 12;
+    if (bands <= kSplitTarget) return pr.m == 1 ? one_order : mean > (one_order ? (spills ? 20 : 0) : 48);
+    return pr.m == 2 && mean > (spills ? 192 : (dtype == 0 ? 8 : (one_order ? 32 : (tri ? 100 : 64))));
 }
 
 // How much workspace a layout may take for speed alone.

@@ -44,7 +44,7 @@ def test_passes_where_they_are_faster(m, N, R, order, dtype, stat, passes):
 
 @pytest.mark.parametrize("m,N,J,passes", [
     (1, 300, 1.4, False), (1, 300, np.array([1.4, 1.4, 1.0, 1.4]), True),
-    (2, 30, 1.0, False), (2, 30, np.array([1.0, 0.6, 1.0, 1.0]), True), (2, 60, np.array([1.0, 0.6, 1.0, 1.0]), False),
+    (2, 30, 1.0, False), (2, 30, np.array([1.0, 0.6, 1.0, 1.0]), True), (2, 60, np.array([1.0, 0.6, 1.0, 1.0]), False), (2, 40, np.array([1.0, 0.6, 1.0, 1.0]), True),
 ])
 def test_two_orders(m, N, J, passes):
     """Two a-priori orders are two launches of one pass each, so a small batch
